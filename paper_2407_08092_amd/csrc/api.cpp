@@ -289,6 +289,7 @@ hipError_t launch_any(ddq_lattice* L, const HopArgs<R>& a, int mode, bool dag, i
       return launch_hop_rb(b, mode, nrhs, L->stream);
     }
   }
+  if (!t && hop_split_takes(L->geo, sizeof(pair<R>), nrhs)) return launch_hop_split<R>(a, mode, dag, nrhs, L->stream);
   // one right-hand side per thread: the workgroup order of an nb = 0 tile set for
   // nrhs, else slab order
   b.tile = MrTile{};
@@ -356,7 +357,7 @@ hipError_t run_hop(ddq_lattice* L, const HopArgs<R>& a, int mode, bool dag, int 
 
 // the 16-bit-storage stencil: kernel A (M_HOP_CLINV) or kernel B (M_APPLY / M_RICH)
 hipError_t run_hop16(ddq_lattice* L, int prec, int nrhs, int mode, const void* in, const void* x, const void* b,
-                     void* out, float omega) {
+                     void* out, float omega, bool sweep) {
   Hop16Args a{};
   const int p_out = mode == M_HOP_CLINV ? 1 : 0;
   a.g = L->geo;
@@ -370,30 +371,34 @@ hipError_t run_hop16(ddq_lattice* L, int prec, int nrhs, int mode, const void* i
   a.out = (u4_t*)out;
   a.omega = omega;
   a.nrhs = nrhs;
+  a.sweep = sweep;
   // workgroup order: that of the lattice's FP32 tile for this count, else slab order
   const MrTile* t = nrhs > 1 ? L->tile_for(nrhs) : nullptr;
   a.chunk = t ? t->xmap : XMAP_SLAB;
-  if (!L->prof_on || g_no_alloc_call) return launch_hop16(h16_kind(prec), a, mode, L->stream);
+  auto launch = [&]() {
+    return !t && hop_split_takes(L->geo, 4, nrhs) ? launch_hop16_split(h16_kind(prec), a, mode, L->stream)
+                                                  : launch_hop16(h16_kind(prec), a, mode, L->stream);
+  };
+  if (!L->prof_on || g_no_alloc_call) return launch();
   std::string name = std::string(mode_name(mode)) + (prec == DDQ_BF16 ? "_bf16" : "_f16") +
                      (L->h16_clover32 ? "_c32" : "") +
                      (nrhs > 1 ? "_x" + std::to_string(nrhs) : "");
-  return prof_launch(L, name, hop_bytes(L, prec, mode, nrhs),
-                     [&]() { return launch_hop16(h16_kind(prec), a, mode, L->stream); });
+  return prof_launch(L, name, hop_bytes(L, prec, mode, nrhs), launch);
 }
 
 // u: work space for u_o (nrhs parity vectors of prec); null selects the lattice's own
 int schur16(ddq_lattice* L, int prec, int nrhs, const void* x, void* y, void* u = nullptr) {
   if (!u) u = L->tmp[prec].p;
-  HIPCHK(run_hop16(L, prec, nrhs, M_HOP_CLINV, x, nullptr, nullptr, u, 0.f));
-  HIPCHK(run_hop16(L, prec, nrhs, M_APPLY, u, x, nullptr, y, 0.f));
+  HIPCHK(run_hop16(L, prec, nrhs, M_HOP_CLINV, x, nullptr, nullptr, u, 0.f, false));
+  HIPCHK(run_hop16(L, prec, nrhs, M_APPLY, u, x, nullptr, y, 0.f, false));
   return DDQ_OK;
 }
 
 int sweeps16(ddq_lattice* L, int prec, int nrhs, void* x, const void* b, int n, float omega) {
   void* u = L->tmp[prec].p;
   for (int k = 0; k < n; ++k) {
-    HIPCHK(run_hop16(L, prec, nrhs, M_HOP_CLINV, x, nullptr, nullptr, u, 0.f));
-    HIPCHK(run_hop16(L, prec, nrhs, M_RICH, u, x, b, x, omega));
+    HIPCHK(run_hop16(L, prec, nrhs, M_HOP_CLINV, x, nullptr, nullptr, u, 0.f, true));
+    HIPCHK(run_hop16(L, prec, nrhs, M_RICH, u, x, b, x, omega, true));
   }
   return DDQ_OK;
 }
@@ -444,8 +449,9 @@ HopArgs<R> hop_args(const ddq_lattice* L, int prec, int p_out) {
 
 // u_o = A_oo^-1 H_oe x_e  (kernel A)
 template <typename R>
-hipError_t kernel_A(ddq_lattice* L, int prec, int nrhs, const pair<R>* x, pair<R>* u, bool dag) {
+hipError_t kernel_A(ddq_lattice* L, int prec, int nrhs, const pair<R>* x, pair<R>* u, bool dag, bool sweep = false) {
   HopArgs<R> a = hop_args<R>(L, prec, 1);
+  a.sweep = sweep;
   a.in = x;
   a.out = u;
   return run_hop<R>(L, a, M_HOP_CLINV, dag, nrhs);
@@ -461,6 +467,7 @@ hipError_t kernel_B(ddq_lattice* L, int prec, int nrhs, int mode, const pair<R>*
   a.b = b;
   a.out = out;
   a.omega = omega;
+  a.sweep = mode == M_RICH;
   return run_hop<R>(L, a, mode, dag, nrhs);
 }
 
@@ -546,7 +553,7 @@ int sweeps(ddq_lattice* L, int prec, int nrhs, pair<R>* x, const pair<R>* b, int
       CHK(sweep_chunked<R>(L, prec, x, b, u, x, omega, nc, M_RICH, false));
       continue;
     }
-    HIPCHK(kernel_A<R>(L, prec, nrhs, x, u, false));
+    HIPCHK(kernel_A<R>(L, prec, nrhs, x, u, false, true));
     HIPCHK(kernel_B<R>(L, prec, nrhs, M_RICH, u, x, b, x, omega, false));
   }
   return DDQ_OK;

@@ -68,6 +68,12 @@ template <typename R> __device__ __forceinline__ void cfma_conj(cpx<R>& acc, cpx
 #ifndef DDQ_STREAM_AUX
 #define DDQ_STREAM_AUX 2
 #endif
+// What a one-right-hand-side launch leaves in the 256 MB Infinity Cache.  A non-temporal
+// access does not allocate there, so the policy picks the fields that the next launch should
+// find: nothing, the vectors (x, u_o, b: read and written up to three times a sweep), or the
+// vectors and the clover blocks.
+enum CachePolicy { CP_STREAM = 0, CP_VECTORS = 1, CP_VECTORS_CLOVER = 2 };
+constexpr int cp_clover_aux(int cp) { return cp >= CP_VECTORS_CLOVER ? 0 : DDQ_STREAM_AUX; }
 // cache-policy bits of the spinor loads (reused by the eight neighbours)
 #ifndef DDQ_SPINOR_AUX
 #define DDQ_SPINOR_AUX 0
@@ -156,8 +162,11 @@ __device__ __forceinline__ void store_fence() {
 #ifndef DDQ_OWN_AUX
 #define DDQ_OWN_AUX 2
 #endif
+constexpr int cp_own_aux(int cp) { return cp >= CP_VECTORS ? 0 : DDQ_OWN_AUX; }
+constexpr int cp_store_aux(int cp) { return cp >= CP_VECTORS ? 0 : DDQ_STORE_AUX; }
+template <int AUX = DDQ_STORE_AUX>
 __device__ __forceinline__ void st16(const Field& f, int row, uint32_t off, u4_t v) {
-  __builtin_amdgcn_raw_buffer_store_b128(v, f.rsrc, (int)off, (int)(row * f.row_bytes), DDQ_STORE_AUX);
+  __builtin_amdgcn_raw_buffer_store_b128(v, f.rsrc, (int)off, (int)(row * f.row_bytes), AUX);
   store_fence();
 }
 
@@ -303,7 +312,7 @@ __device__ __forceinline__ Spinor<R> load_spinor(const Field& v, uint32_t off) {
     for (int b = 0; b < 3; ++b) s.c[a][b] = c[3 * a + b];
   return s;
 }
-template <typename R>
+template <typename R, int AUX = DDQ_STORE_AUX>
 __device__ __forceinline__ void store_spinor(const Field& v, uint32_t off, const Spinor<R>& s) {
   cpx<R> c[SPINOR_ROWS];
 #pragma unroll
@@ -311,7 +320,7 @@ __device__ __forceinline__ void store_spinor(const Field& v, uint32_t off, const
 #pragma unroll
     for (int b = 0; b < 3; ++b) c[3 * a + b] = s.c[a][b];
 #pragma unroll
-  for (int k = 0; k < SPINOR_ROWS / CPE<R>; ++k) st16(v, k, off, pack<R>(c + k * CPE<R>));
+  for (int k = 0; k < SPINOR_ROWS / CPE<R>; ++k) st16<AUX>(v, k, off, pack<R>(c + k * CPE<R>));
 }
 
 // Spin projection (1 + sg * g_mu) psi in the chiral basis.  With
@@ -374,27 +383,36 @@ __device__ __forceinline__ void accumulate(Spinor<R>& acc, const Half<R>& h, R s
 template <typename R> struct Link { cpx<R> u[9]; };
 
 // one direction's link field: LINK_ROWS complex rows (U_mu(x), then U_mu(x - mu)^H)
-template <typename R>
+template <typename R, int AUX = DDQ_STREAM_AUX>
 __device__ __forceinline__ Link<R> load_link_half(const Field& U, int half, uint32_t off) {
   Link<R> l;
-  load_rows<R, DDQ_STREAM_AUX>(U, 9 * half, 9, off, l.u);  // FP64 only: 9 rows = 9 elements
+  load_rows<R, AUX>(U, 9 * half, 9, off, l.u);  // FP64 only: 9 rows = 9 elements
   return l;
+}
+// conj(a b - c d) as written here in every kernel: left to the compiler, the way the products
+// and sums are fused differs from one kernel to the next
+template <typename R>
+__device__ __forceinline__ cpx<R> conj_cross(cpx<R> a, cpx<R> b, cpx<R> c, cpx<R> d) {
+#pragma clang fp contract(off)
+  const R re = fma(a.r, b.r, fma(-a.i, b.i, fma(-c.r, d.r, c.i * d.i)));
+  const R im = fma(c.r, d.i, fma(c.i, d.r, fma(-a.r, b.i, -(a.i * b.r))));
+  return {re, im};
 }
 // SU(3) from its first two rows: row 2 = conj(row 0 x row 1)
 template <typename R>
 __device__ __forceinline__ void su3_third_row(Link<R>& l) {
-  l.u[6] = conj(l.u[1] * l.u[5] - l.u[2] * l.u[4]);
-  l.u[7] = conj(l.u[2] * l.u[3] - l.u[0] * l.u[5]);
-  l.u[8] = conj(l.u[0] * l.u[4] - l.u[1] * l.u[3]);
+  l.u[6] = conj_cross(l.u[1], l.u[5], l.u[2], l.u[4]);
+  l.u[7] = conj_cross(l.u[2], l.u[3], l.u[0], l.u[5]);
+  l.u[8] = conj_cross(l.u[0], l.u[4], l.u[1], l.u[3]);
 }
 
 // 12-real storage (LINK12_ROWS complex rows per direction: the first two rows of
 // U_mu(x), then of U_mu(x - mu)^H); the third rows are rebuilt
 constexpr int LINK12_ROWS = 12;
-template <typename R>
+template <typename R, int AUX = DDQ_STREAM_AUX>
 __device__ __forceinline__ void load_link_pair12(const Field& U, uint32_t off, Link<R>& fwd, Link<R>& bwd) {
   cpx<R> c[LINK12_ROWS];
-  load_rows<R, DDQ_STREAM_AUX>(U, 0, LINK12_ROWS, off, c);
+  load_rows<R, AUX>(U, 0, LINK12_ROWS, off, c);
 #pragma unroll
   for (int e = 0; e < 6; ++e) {
     fwd.u[e] = c[e];
@@ -403,10 +421,10 @@ __device__ __forceinline__ void load_link_pair12(const Field& U, uint32_t off, L
   su3_third_row(fwd);  // the backward link's third row is rebuilt where it is used
 }
 
-template <typename R>
+template <typename R, int AUX = DDQ_STREAM_AUX>
 __device__ __forceinline__ void load_link_pair(const Field& U, uint32_t off, Link<R>& fwd, Link<R>& bwd) {
   cpx<R> c[LINK_ROWS];
-  load_rows<R, DDQ_STREAM_AUX>(U, 0, LINK_ROWS, off, c);
+  load_rows<R, AUX>(U, 0, LINK_ROWS, off, c);
 #pragma unroll
   for (int e = 0; e < 9; ++e) {
     fwd.u[e] = c[e];
@@ -462,13 +480,13 @@ __device__ __forceinline__ void clover_block_apply(const cpx<R>* sl, const cpx<R
 
 // out = A psi for the two blocks of a site (block 0: spins 0,1; block 1: spins 2,3).
 // C: the clover field (bfield, CLOVER_ROWS / CPE element rows); off = boff(i, ...)
-template <typename R>
+template <typename R, int AUX = DDQ_STREAM_AUX>
 __device__ __forceinline__ Spinor<R> clover_mul(const Field& C, uint32_t off, const Spinor<R>& p) {
   Spinor<R> o;
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
     cpx<R> sl[18];
-    load_rows<R, DDQ_STREAM_AUX>(C, 18 * b, 18, off, sl);
+    load_rows<R, AUX>(C, 18 * b, 18, off, sl);
     cpx<R> in[6], out[6];
 #pragma unroll
     for (int k = 0; k < 6; ++k) in[k] = p.c[2 * b + k / 3][k % 3];

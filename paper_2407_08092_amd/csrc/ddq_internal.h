@@ -107,8 +107,24 @@ struct HopArgs {
   int nrhs;                  // right-hand sides of the launch
   long long rhs_stride;      // complex elements between right-hand sides
   MrTile tile;               // FP32 multi-right-hand-side tile (nb = 0: one right-hand side per thread)
+  bool sweep;                // part of a Richardson sweep: the next launches read the same fields (cache_policy)
   int t_lo, t_cnt;           // one right-hand side: only output sites of slices [t_lo, t_lo + t_cnt) (t_cnt 0: all)
 };
+
+// Cache policy of a sweep's launches on vh sites a parity with one right-hand side (a single
+// apply's results are not read by the launches that follow and stream: kept, 24^3 x 48 FP64 272
+// -> 281 us), by what fits: three vectors of vec bytes a site (x, u_o, b), then two clover fields of clov bytes a site.
+// The line lies above the cache's 256 MB because not every row is live at once.  Microseconds
+// a sweep, streaming everything against the policy taken: FP64 24^3 x 48 (191 MB of vectors)
+// 285 -> 279, 32^4 (302 MB) 412 -> 398, 24^3 x 96 (382 MB: streams) 545, vectors kept 555; FP32
+// 12-real 32^3 x 64 (302 MB) 381 -> 339; FP16 24^3 x 48 (127 MB of vectors and clover) 65 -> 60,
+// 24^3 x 96 (308 MB) 121 -> 110, 48^3 x 96 (764 MB of vectors: streams) 909, kept 975.
+constexpr long long CACHE_FIELDS = 320LL << 20;
+inline int cache_policy(bool sweep, int vh, int vec, int clov) {
+  if (!sweep) return CP_STREAM;
+  const long long v = 3LL * vh * vec, c = 2LL * vh * clov;
+  return v + c <= CACHE_FIELDS ? CP_VECTORS_CLOVER : v <= CACHE_FIELDS ? CP_VECTORS : CP_STREAM;
+}
 
 #ifndef DDQ_HOP_BLOCK
 #define DDQ_HOP_BLOCK 256
@@ -121,6 +137,12 @@ hipError_t launch_hop(const HopArgs<R>& a, int mode, bool dagger, int nrhs, hipS
 // (M_HOP_CLINV, M_APPLY, M_RICH): the same bytes without gathers or arithmetic
 template <typename R>
 hipError_t launch_hop_stream(const HopArgs<R>& a, int mode, hipStream_t s);
+
+// the same launches (any mode; no tile) on four threads per site, bit for bit the results of
+// launch_hop and launch_hop16: for launches of few sites (hop_split.hip)
+bool hop_split_takes(const Geo& g, int bytes_per_complex, int nrhs);
+template <typename R>
+hipError_t launch_hop_split(const HopArgs<R>& a, int mode, bool dagger, int nrhs, hipStream_t s);
 
 // register-blocked FP32 multi-right-hand-side stencil for modes M_HOP_CLINV, M_APPLY
 // and M_RICH (not daggered); a.tile.nb in [2, MR_MAX_NB] must divide nrhs.  Returns
@@ -180,9 +202,11 @@ struct Hop16Args {
   float omega;
   int nrhs;
   int nb;     // right-hand sides per thread, 1..3 (0: the largest of 3, 2, 1 dividing nrhs)
+  bool sweep;  // part of a Richardson sweep (cache_policy)
   int chunk;  // XCD order of the workgroups (tile_site): 0 dispatcher order, c > 0 chunks, XMAP_SLAB
 };
 hipError_t launch_hop16(int kind, const Hop16Args& a, int mode, hipStream_t s);
+hipError_t launch_hop16_split(int kind, const Hop16Args& a, int mode, hipStream_t s);
 hipError_t launch_parity_to_h16(int kind, void* y, const d2_t* x, double scale, int nrhs, int vh, hipStream_t s);
 hipError_t launch_parity_from_h16(int kind, d2_t* y, const void* x, double scale, int nrhs, int vh, hipStream_t s);
 hipError_t launch_h16_to_f32(int kind, void* y, const void* x, float scale, int nrhs, int vh, hipStream_t s);

@@ -65,9 +65,10 @@ static int one_rhs_grid(const Geo& g, int t_cnt = 0) {
 #endif
 }
 
-template <typename R, int MODE, bool DAG, bool L12, bool MR>
+template <typename R, int MODE, bool DAG, bool L12, bool MR, int CP>
 __global__ void __launch_bounds__(HOP_BLOCK) __attribute__((amdgpu_waves_per_eu(HOP_WAVES<R, L12>::value)))
 hop_kernel(HopArgs<R> a) {
+  constexpr int OWN = cp_own_aux(CP), ST = cp_store_aux(CP), CLV = cp_clover_aux(CP);
   const int vh = a.g.Vh;
   int i, rhs;
   if constexpr (!MR) {
@@ -120,25 +121,25 @@ hop_kernel(HopArgs<R> a) {
 
   const Field out = vfield(a.out + roff, SP_E, vh);  // may alias a.x (in-place Richardson)
   if constexpr (MODE == M_HOP_CLINV) {
-    store_spinor<R>(out, off, clover_mul<R>(cl, coff, acc));
+    store_spinor<R, ST>(out, off, clover_mul<R, CLV>(cl, coff, acc));
   } else if constexpr (MODE == M_RECON) {
-    Spinor<R> bb = load_spinor<R, DDQ_OWN_AUX>(vfield(a.b + roff, SP_E, vh), off);
+    Spinor<R> bb = load_spinor<R, OWN>(vfield(a.b + roff, SP_E, vh), off);
 #pragma unroll
     for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
       for (int cc = 0; cc < 3; ++cc) bb.c[sp][cc] = bb.c[sp][cc] + acc.c[sp][cc];
-    store_spinor<R>(out, off, clover_mul<R>(cl, coff, bb));
+    store_spinor<R, ST>(out, off, clover_mul<R, CLV>(cl, coff, bb));
   } else if constexpr (MODE == M_APPLY) {
-    Spinor<R> cx = clover_mul<R>(cl, coff, load_spinor<R, DDQ_OWN_AUX>(vfield(a.x + roff, SP_E, vh), off));
+    Spinor<R> cx = clover_mul<R, CLV>(cl, coff, load_spinor<R, OWN>(vfield(a.x + roff, SP_E, vh), off));
 #pragma unroll
     for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
       for (int cc = 0; cc < 3; ++cc) cx.c[sp][cc] = cx.c[sp][cc] - acc.c[sp][cc];
-    store_spinor<R>(out, off, cx);
+    store_spinor<R, ST>(out, off, cx);
   } else if constexpr (MODE == M_RICH) {
-    Spinor<R> xx = load_spinor<R, DDQ_OWN_AUX>(vfield(a.x + roff, SP_E, vh), off);
-    Spinor<R> bb = load_spinor<R, DDQ_OWN_AUX>(vfield(a.b + roff, SP_E, vh), off);
-    Spinor<R> cx = clover_mul<R>(cl, coff, xx);
+    Spinor<R> xx = load_spinor<R, OWN>(vfield(a.x + roff, SP_E, vh), off);
+    Spinor<R> bb = load_spinor<R, OWN>(vfield(a.b + roff, SP_E, vh), off);
+    Spinor<R> cx = clover_mul<R, CLV>(cl, coff, xx);
 #pragma unroll
     for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
@@ -146,22 +147,22 @@ hop_kernel(HopArgs<R> a) {
         cpx<R> r = bb.c[sp][cc] - cx.c[sp][cc] + acc.c[sp][cc];
         xx.c[sp][cc] = xx.c[sp][cc] + a.omega * r;
       }
-    store_spinor<R>(out, off, xx);
+    store_spinor<R, ST>(out, off, xx);
   } else if constexpr (MODE == M_RESID) {
-    Spinor<R> bb = load_spinor<R, DDQ_OWN_AUX>(vfield(a.b + roff, SP_E, vh), off);
-    Spinor<R> cx = clover_mul<R>(cl, coff, load_spinor<R, DDQ_OWN_AUX>(vfield(a.x + roff, SP_E, vh), off));
+    Spinor<R> bb = load_spinor<R, OWN>(vfield(a.b + roff, SP_E, vh), off);
+    Spinor<R> cx = clover_mul<R, CLV>(cl, coff, load_spinor<R, OWN>(vfield(a.x + roff, SP_E, vh), off));
 #pragma unroll
     for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
       for (int cc = 0; cc < 3; ++cc) bb.c[sp][cc] = bb.c[sp][cc] - cx.c[sp][cc] + acc.c[sp][cc];
-    store_spinor<R>(out, off, bb);
+    store_spinor<R, ST>(out, off, bb);
   } else {  // M_PREP
-    Spinor<R> bb = load_spinor<R, DDQ_OWN_AUX>(vfield(a.b + roff, SP_E, vh), off);
+    Spinor<R> bb = load_spinor<R, OWN>(vfield(a.b + roff, SP_E, vh), off);
 #pragma unroll
     for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
       for (int cc = 0; cc < 3; ++cc) bb.c[sp][cc] = bb.c[sp][cc] + acc.c[sp][cc];
-    store_spinor<R>(out, off, bb);
+    store_spinor<R, ST>(out, off, bb);
   }
 }
 
@@ -276,20 +277,29 @@ static hipError_t launch_mode(const HopArgs<R>& a, bool dagger, int nrhs, hipStr
   // 12-real links exist for FP32 storage only
   const bool l12 = sizeof(R) == 4 && a.link12;
   constexpr bool F32 = sizeof(R) == 4;
-#define DDQ_HOP_LAUNCH(D, L, M) hipLaunchKernelGGL((hop_kernel<R, MODE, D, L, M>), grid, block, 0, s, a)
+#define DDQ_HOP_LAUNCH(D, L, M, CP) hipLaunchKernelGGL((hop_kernel<R, MODE, D, L, M, CP>), grid, block, 0, s, a)
+#define DDQ_HOP_LAUNCH_D(L, M, CP)        \
+  if (dagger)                             \
+    DDQ_HOP_LAUNCH(true, L, M, CP);       \
+  else                                    \
+    DDQ_HOP_LAUNCH(false, L, M, CP)
+#define DDQ_HOP_LAUNCH_L(M, CP)           \
+  if (l12) {                              \
+    DDQ_HOP_LAUNCH_D(F32, M, CP);         \
+  } else {                                \
+    DDQ_HOP_LAUNCH_D(false, M, CP);       \
+  }
   if (nrhs > 1) {
-    if (l12) {
-      if (dagger) DDQ_HOP_LAUNCH(true, F32, true); else DDQ_HOP_LAUNCH(false, F32, true);
-    } else {
-      if (dagger) DDQ_HOP_LAUNCH(true, false, true); else DDQ_HOP_LAUNCH(false, false, true);
-    }
+    DDQ_HOP_LAUNCH_L(true, CP_STREAM)
   } else {
-    if (l12) {
-      if (dagger) DDQ_HOP_LAUNCH(true, F32, false); else DDQ_HOP_LAUNCH(false, F32, false);
-    } else {
-      if (dagger) DDQ_HOP_LAUNCH(true, false, false); else DDQ_HOP_LAUNCH(false, false, false);
+    switch (cache_policy(a.sweep, a.g.Vh, SPINOR_ROWS * (int)sizeof(pair<R>), CLOVER_ROWS * (int)sizeof(pair<R>))) {
+      case CP_VECTORS_CLOVER: DDQ_HOP_LAUNCH_L(false, CP_VECTORS_CLOVER) break;
+      case CP_VECTORS: DDQ_HOP_LAUNCH_L(false, CP_VECTORS) break;
+      default: DDQ_HOP_LAUNCH_L(false, CP_STREAM) break;
     }
   }
+#undef DDQ_HOP_LAUNCH_L
+#undef DDQ_HOP_LAUNCH_D
 #undef DDQ_HOP_LAUNCH
   return hipGetLastError();
 }
@@ -304,11 +314,15 @@ hipError_t launch_hop(const HopArgs<R>& a0, int mode, bool dagger, int nrhs, hip
   if (a.nblk < 0) return hipErrorInvalidValue;
   switch (mode) {
     case M_HOP_CLINV: return launch_mode<R, M_HOP_CLINV>(a, dagger, nrhs, s);
-    case M_RECON: return launch_mode<R, M_RECON>(a, dagger, nrhs, s);
     case M_APPLY: return launch_mode<R, M_APPLY>(a, dagger, nrhs, s);
     case M_RICH: return launch_mode<R, M_RICH>(a, dagger, nrhs, s);
-    case M_RESID: return launch_mode<R, M_RESID>(a, dagger, nrhs, s);
-    case M_PREP: return launch_mode<R, M_PREP>(a, dagger, nrhs, s);
+  }
+  if constexpr (sizeof(R) == 8) {  // eq. 2 and the residual run in FP64
+    switch (mode) {
+      case M_RECON: return launch_mode<R, M_RECON>(a, dagger, nrhs, s);
+      case M_RESID: return launch_mode<R, M_RESID>(a, dagger, nrhs, s);
+      case M_PREP: return launch_mode<R, M_PREP>(a, dagger, nrhs, s);
+    }
   }
   return hipErrorInvalidValue;
 }

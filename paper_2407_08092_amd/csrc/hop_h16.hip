@@ -11,63 +11,9 @@
 // Per even site the Schur apply moves 944 bytes (FP32 with 12-real links: 1824).
 // Link and clover fields use the blocked 64-site layout of the other paths.
 #include "hop_common.h"
+#include "hop_h16.h"
 
 namespace ddq {
-
-typedef unsigned short u16_t;
-
-template <typename S>
-__device__ __forceinline__ float h2f(u16_t b) {
-  return (float)__builtin_bit_cast(S, b);
-}
-template <typename S>
-__device__ __forceinline__ u16_t f2h(float f) {
-  return __builtin_bit_cast(u16_t, (S)f);
-}
-
-// element <-> four complex numbers; complex j is word j (re: low half, im: high half)
-template <typename S>
-__device__ __forceinline__ void unpack4(u4_t q, cpx<float>* c) {
-#pragma unroll
-  for (int j = 0; j < 4; ++j) c[j] = {h2f<S>((u16_t)(q[j] & 0xffffu)), h2f<S>((u16_t)(q[j] >> 16))};
-}
-template <typename S>
-__device__ __forceinline__ u4_t pack4(const cpx<float>* c) {
-  u4_t q;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) q[j] = (unsigned)f2h<S>(c[j].r) | ((unsigned)f2h<S>(c[j].i) << 16);
-  return q;
-}
-
-constexpr int SP16_E = 3;   // element rows of a spinor
-constexpr int LK16_E = 3;   // element rows of one direction's 12-real link pair
-constexpr int CL16_E = 10;  // element rows of a site's clover (2 blocks x 5)
-
-template <typename S>
-__device__ __forceinline__ Spinor<float> unpack_spinor(const u4_t (&q)[SP16_E]) {
-  cpx<float> c[12];
-#pragma unroll
-  for (int e = 0; e < SP16_E; ++e) unpack4<S>(q[e], c + 4 * e);
-  Spinor<float> s;
-#pragma unroll
-  for (int k = 0; k < 12; ++k) s.c[k / 3][k % 3] = c[k];
-  return s;
-}
-template <typename S, int AUX = DDQ_SPINOR_AUX>
-__device__ __forceinline__ Spinor<float> load_spinor16(const Field& v, uint32_t off) {
-  u4_t q[SP16_E];
-#pragma unroll
-  for (int e = 0; e < SP16_E; ++e) q[e] = ld16<AUX>(v, e, off);
-  return unpack_spinor<S>(q);
-}
-template <typename S>
-__device__ __forceinline__ void store_spinor16(const Field& v, uint32_t off, const Spinor<float>& s) {
-  cpx<float> c[12];
-#pragma unroll
-  for (int k = 0; k < 12; ++k) c[k] = s.c[k / 3][k % 3];
-#pragma unroll
-  for (int e = 0; e < SP16_E; ++e) st16(v, e, off, pack4<S>(c + 4 * e));
-}
 
 // raw loads of one hop for nb right-hand sides, issued one hop ahead of their use
 template <int NB>
@@ -135,10 +81,10 @@ __device__ __forceinline__ void steps16(Spinor<float> (&acc)[NB], const Raw16<NB
 }
 
 // the 18 slots of clover block b (element rows 5b..5b+4; the last two slots pad)
-template <typename S>
+template <typename S, int AUX>
 __device__ __forceinline__ void clover_slots16(const Field& C, uint32_t off, int b, cpx<float> (&sl)[20]) {
 #pragma unroll
-  for (int e = 0; e < 5; ++e) unpack4<S>(ld16<DDQ_STREAM_AUX>(C, 5 * b + e, off), sl + 4 * e);
+  for (int e = 0; e < 5; ++e) unpack4<S>(ld16<AUX>(C, 5 * b + e, off), sl + 4 * e);
 }
 
 // spinor rows of clover block b (spins 2b, 2b+1: rows 6b..6b+5)
@@ -155,10 +101,11 @@ __device__ __forceinline__ void set_block_rows(Spinor<float>& s, int b, const cp
 // of one group of NB right-hand sides (tile_site); the links and clover slots of the
 // site are loaded once for the NB spinors.
 // C32: the clover blocks come from the FP32 field (CLOVER_ROWS complex rows, two per
-// 16-byte element) instead of the 16-bit one
-template <typename S, int MODE, int NB, bool C32>
+// 16-byte element) instead of the 16-bit one; CP: cache policy (one right-hand side)
+template <typename S, int MODE, int NB, bool C32, int CP>
 __global__ void __launch_bounds__(HOP_BLOCK) __attribute__((amdgpu_waves_per_eu(NB > 1 ? 2 : 4)))
 hop16_kernel(Hop16Args a) {
+  constexpr int OWN = cp_own_aux(CP), ST = cp_store_aux(CP), CLV = cp_clover_aux(CP);
   const int vh = a.g.Vh;
   int i, rg;
   if (!tile_site(a.g, (int)blockIdx.x, a.nrhs / NB, a.chunk, HOP_BLOCK, (int)threadIdx.x, i, rg)) return;
@@ -190,9 +137,9 @@ hop16_kernel(Hop16Args a) {
   const uint32_t off = voff(i);
   auto slots = [&](int b, cpx<float>(&sl)[20]) {
     if constexpr (C32)
-      load_rows<float, DDQ_STREAM_AUX>(cl, 18 * b, 18, coff, sl);
+      load_rows<float, CLV>(cl, 18 * b, 18, coff, sl);
     else
-      clover_slots16<S>(cl, coff, b, sl);
+      clover_slots16<S, CLV>(cl, coff, b, sl);
   };
   // epilogue: per right-hand side, both clover blocks (their slots loaded once
   // for the NB spinors; with one right-hand side, block by block)
@@ -205,8 +152,8 @@ hop16_kernel(Hop16Args a) {
   for (int q = 0; q < NB; ++q) {
     const size_t roff = (size_t)(r0 + q) * SP16_E * (size_t)vh;
     Spinor<float> xx, bb;
-    if constexpr (MODE != M_HOP_CLINV) xx = load_spinor16<S, DDQ_OWN_AUX>(vfield(a.x + roff, SP16_E, vh), off);
-    if constexpr (MODE == M_RICH) bb = load_spinor16<S, DDQ_OWN_AUX>(vfield(a.b + roff, SP16_E, vh), off);
+    if constexpr (MODE != M_HOP_CLINV) xx = load_spinor16<S, OWN>(vfield(a.x + roff, SP16_E, vh), off);
+    if constexpr (MODE == M_RICH) bb = load_spinor16<S, OWN>(vfield(a.b + roff, SP16_E, vh), off);
     Spinor<float> res;
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
@@ -233,16 +180,16 @@ hop16_kernel(Hop16Args a) {
       }
       set_block_rows(res, b, o);
     }
-    store_spinor16<S>(vfield(a.out + roff, SP16_E, vh), off, res);  // may alias a.x (in place)
+    store_spinor16<S, ST>(vfield(a.out + roff, SP16_E, vh), off, res);  // may alias a.x (in place)
   }
 }
 
-template <typename S, int NB, bool C32>
+template <typename S, int NB, bool C32, int CP>
 static hipError_t launch16_c(const Hop16Args& a, int mode, dim3 grid, dim3 block, hipStream_t s) {
   switch (mode) {
-    case M_HOP_CLINV: hipLaunchKernelGGL((hop16_kernel<S, M_HOP_CLINV, NB, C32>), grid, block, 0, s, a); break;
-    case M_APPLY: hipLaunchKernelGGL((hop16_kernel<S, M_APPLY, NB, C32>), grid, block, 0, s, a); break;
-    case M_RICH: hipLaunchKernelGGL((hop16_kernel<S, M_RICH, NB, C32>), grid, block, 0, s, a); break;
+    case M_HOP_CLINV: hipLaunchKernelGGL((hop16_kernel<S, M_HOP_CLINV, NB, C32, CP>), grid, block, 0, s, a); break;
+    case M_APPLY: hipLaunchKernelGGL((hop16_kernel<S, M_APPLY, NB, C32, CP>), grid, block, 0, s, a); break;
+    case M_RICH: hipLaunchKernelGGL((hop16_kernel<S, M_RICH, NB, C32, CP>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -253,7 +200,17 @@ static hipError_t launch16_nb(const Hop16Args& a, int mode, hipStream_t s) {
   const long long nb = tile_grid_sites(a.g, HOP_BLOCK, a.nrhs / NB, a.chunk);
   if (nb > 0x7fffffffLL) return hipErrorInvalidValue;
   dim3 grid((unsigned)nb), block(HOP_BLOCK);
-  return a.clov32 ? launch16_c<S, NB, true>(a, mode, grid, block, s) : launch16_c<S, NB, false>(a, mode, grid, block, s);
+#define DDQ_H16_LAUNCH(CP) \
+  return a.clov32 ? launch16_c<S, NB, true, CP>(a, mode, grid, block, s) : launch16_c<S, NB, false, CP>(a, mode, grid, block, s)
+  if constexpr (NB == 1) {
+    if (a.nrhs == 1) {
+      const int cp = cache_policy(a.sweep, a.g.Vh, SP16_E * 16, a.clov32 ? CLOVER_ROWS * 8 : CL16_E * 16);
+      if (cp == CP_VECTORS_CLOVER) DDQ_H16_LAUNCH(CP_VECTORS_CLOVER);
+      if (cp == CP_VECTORS) DDQ_H16_LAUNCH(CP_VECTORS);
+    }
+  }
+  DDQ_H16_LAUNCH(CP_STREAM);
+#undef DDQ_H16_LAUNCH
 }
 
 template <typename S>

@@ -1,0 +1,370 @@
+// hop_split.hip -- the stencil of hop.hip / hop_h16.hip for launches of few sites: four
+// threads per output site, one per direction.
+//
+// The one-thread-per-site kernels walk a site's eight hops one after the other with one
+// hop's loads in flight, about eight memory latencies per wavefront.  A large lattice hides
+// them behind its other wavefronts; a small one has none (16^3 x 32: one wavefront per
+// SIMD; 4^4: four on the whole chip) and the chain is its time.  Here a workgroup is 64
+// sites x 4 wavefronts: wavefront w sums up both hops of direction w, so all of a site's
+// neighbour and link loads are in flight at once, and there are four times the wavefronts.
+// The projected and multiplied half spinors of the eight hops meet in LDS; after the barrier
+// wavefront w forms spin w of the hopping term, adding the hops in the order of hop.hip, and
+// the three rows of the clover block that spin w belongs to.  Every number is formed by the
+// same operations in the same order as in the one-thread kernels, so the results are theirs
+// bit for bit and a launch may take either.
+// What bounds it: the launch itself (about 4 us from one launch to the next) up to 10^4 sites,
+// then the caches' bandwidth; 4^4 FP64 8.4 -> 5.3 us a launch, 16^4 FP32 12.6 -> 8.3, 24^3 x 48
+// FP32 71 -> 62 (6.2 TB/s of its algorithmic bytes).
+#include "hop_common.h"
+#include "hop_h16.h"
+
+namespace ddq {
+
+// Storage policies: how a precision's fields are read and written.  KEEP: the operator's
+// fields fit the Infinity Cache and everything may stay there; else links and results are
+// streamed past it.
+template <typename RR, bool L12, bool KEEP>
+struct SplitR {
+  using R = RR;
+  static constexpr int LINK_AUX = KEEP ? 0 : DDQ_STREAM_AUX, ST_AUX = KEEP ? 0 : DDQ_STORE_AUX;
+  static constexpr int SP_E = SPINOR_ROWS / CPE<R>, CL_E = CLOVER_ROWS / CPE<R>;
+  static constexpr int LK_E = (L12 ? LINK12_ROWS : LINK_ROWS) / CPE<R>;
+  static __device__ __forceinline__ Spinor<R> spinor(const Field& v, uint32_t off) { return load_spinor<R>(v, off); }
+  static __device__ __forceinline__ void links(const Field& U, uint32_t off, Link<R>& f, Link<R>& b) {
+    if constexpr (L12) {
+      load_link_pair12<R, LINK_AUX>(U, off, f, b);
+      su3_third_row(b);
+    } else if constexpr (CPE<R> == 1) {
+      f = load_link_half<R, LINK_AUX>(U, 0, off);
+      b = load_link_half<R, LINK_AUX>(U, 1, off);
+    } else {
+      load_link_pair<R, LINK_AUX>(U, off, f, b);
+    }
+  }
+  static __device__ __forceinline__ void slots(const Field& C, uint32_t off, int b, cpx<R>* sl) {
+    load_rows<R>(C, 18 * b, 18, off, sl);
+  }
+  // complex row r (uniform) of a parity vector
+  static __device__ __forceinline__ cpx<R> row(const Field& v, int r, uint32_t off) {
+    if constexpr (CPE<R> == 1) {
+      cpx<R> c;
+      unpack<R>(ld16(v, r, off), &c);
+      return c;
+    } else {
+      const f2_t q = __builtin_bit_cast(
+          f2_t, __builtin_amdgcn_raw_buffer_load_b64(v.rsrc, (int)(off + 8u * (r & 1)), (int)((r >> 1) * v.row_bytes), 0));
+      return {q.x, q.y};
+    }
+  }
+  static __device__ __forceinline__ void put(const Field& v, int r, uint32_t off, cpx<R> c) {
+    if constexpr (CPE<R> == 1) {
+      __builtin_amdgcn_raw_buffer_store_b128(pack<R>(&c), v.rsrc, (int)off, (int)(r * v.row_bytes), ST_AUX);
+    } else {
+      f2_t q;
+      q.x = c.r;
+      q.y = c.i;
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2_t, q), v.rsrc, (int)(off + 8u * (r & 1)),
+                                            (int)((r >> 1) * v.row_bytes), ST_AUX);
+    }
+  }
+};
+
+template <typename S, bool C32>
+struct Split16 {
+  using R = float;
+  static constexpr int SP_E = SP16_E, LK_E = LK16_E, CL_E = C32 ? CLOVER_ROWS / CPE<float> : CL16_E;
+  static __device__ __forceinline__ Spinor<R> spinor(const Field& v, uint32_t off) { return load_spinor16<S>(v, off); }
+  static __device__ __forceinline__ void links(const Field& U, uint32_t off, Link<R>& f, Link<R>& b) {
+    cpx<R> l[12];
+#pragma unroll
+    for (int e = 0; e < LK16_E; ++e) unpack4<S>(ld16(U, e, off), l + 4 * e);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      f.u[k] = l[k];
+      b.u[k] = l[6 + k];
+    }
+    su3_third_row(f);
+    su3_third_row(b);
+  }
+  static __device__ __forceinline__ void slots(const Field& C, uint32_t off, int b, cpx<R>* sl) {
+    if constexpr (C32) {
+      load_rows<R>(C, 18 * b, 18, off, sl);
+    } else {
+      cpx<R> q[20];
+#pragma unroll
+      for (int e = 0; e < 5; ++e) unpack4<S>(ld16(C, 5 * b + e, off), q + 4 * e);
+#pragma unroll
+      for (int k = 0; k < 18; ++k) sl[k] = q[k];
+    }
+  }
+  static __device__ __forceinline__ cpx<R> row(const Field& v, int r, uint32_t off) {
+    const unsigned q =
+        __builtin_amdgcn_raw_buffer_load_b32(v.rsrc, (int)(off + 4u * (r & 3)), (int)((r >> 2) * v.row_bytes), 0);
+    return {h2f<S>((u16_t)(q & 0xffffu)), h2f<S>((u16_t)(q >> 16))};
+  }
+  static __device__ __forceinline__ void put(const Field& v, int r, uint32_t off, cpx<R> c) {
+    c = in_fp32(c);
+    const unsigned q = (unsigned)f2h<S>(c.r) | ((unsigned)f2h<S>(c.i) << 16);
+    __builtin_amdgcn_raw_buffer_store_b32(q, v.rsrc, (int)(off + 4u * (r & 3)), (int)((r >> 2) * v.row_bytes), 0);
+  }
+};
+
+template <int MU, typename R>
+__device__ __forceinline__ void split_hops(const Spinor<R>& pf, const Spinor<R>& pb, const Link<R>& uf,
+                                           const Link<R>& ub, R sf, R sb, const Nbr& nb, Half<R>& hf, Half<R>& hb) {
+  hf = link_mul<R>(uf, project<MU, R>(pf, sf));
+  hb = link_mul<R>(ub, project<MU, R>(pb, sb));
+  if (MU == 3) {
+    scale_half(hf, (R)nb.sgn_tf);
+    scale_half(hb, (R)nb.sgn_tb);
+  }
+}
+
+// o += spin SP of the spinor that `accumulate` rebuilds from hop (MU, sg)'s half spinor h
+template <int MU, int SP, typename R>
+__device__ __forceinline__ void split_add(cpx<R> (&o)[3], const cpx<R> (*h)[64], int lane, R sg) {
+  // the half spinor's spin that this spin is made of
+  constexpr int S = SP < 2 ? SP : (MU < 2 ? 3 - SP : SP - 2);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const cpx<R> v = h[3 * S + c][lane];
+    if constexpr (SP < 2) {
+      o[c] = o[c] + v;
+    } else {
+      cpx<R> d;
+      if (MU == 0) d = times_i(v);
+      else if (MU == 1) d = SP == 2 ? v : cpx<R>{-v.r, -v.i};
+      else if (MU == 2) d = SP == 2 ? times_i(v) : times_minus_i(v);
+      else d = v;
+      o[c] = o[c] + sg * d;
+    }
+  }
+}
+template <int SP, typename R>
+__device__ __forceinline__ void split_sum(cpx<R> (&o)[3], const cpx<R> (*h)[6][64], int lane, R sf, R sb) {
+  split_add<0, SP, R>(o, h[0], lane, sf);
+  split_add<0, SP, R>(o, h[1], lane, sb);
+  split_add<1, SP, R>(o, h[2], lane, sf);
+  split_add<1, SP, R>(o, h[3], lane, sb);
+  split_add<2, SP, R>(o, h[4], lane, sf);
+  split_add<2, SP, R>(o, h[5], lane, sb);
+  split_add<3, SP, R>(o, h[6], lane, sf);
+  split_add<3, SP, R>(o, h[7], lane, sb);
+}
+
+// rows 3 HF .. 3 HF + 2 of clover_block_apply, each summed in its order
+template <int HF, typename R>
+__device__ __forceinline__ void clover_rows(const cpx<R>* sl, const cpx<R> in[6], cpx<R> out[3]) {
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const int r = 3 * HF + c;
+    const R d = (r & 1) ? sl[r >> 1].i : sl[r >> 1].r;
+    out[c] = d * in[r];
+#pragma unroll
+    for (int j = 0; j < r; ++j) cfma_conj(out[c], sl[tri_slot(j, r)], in[j]);
+#pragma unroll
+    for (int k = r + 1; k < 6; ++k) cfma(out[c], sl[tri_slot(r, k)], in[k]);
+  }
+}
+
+struct SplitArgs {
+  Geo g;
+  int p_out;
+  const void *in, *links, *clov, *x, *b;
+  void* out;
+  double omega;
+  int nrhs;
+  int dagger;
+  int slab;         // slab order; else the groups of 64 sites in a row
+  int t_lo, t_cnt;  // output sites of slices [t_lo, t_lo + t_cnt)
+};
+
+template <class P, int MODE>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(typename P::R) == 8 ? 2 : 3)))
+hop_split_kernel(SplitArgs a) {
+  using R = typename P::R;
+  __shared__ cpx<R> hs[8][6][64];
+  __shared__ cpx<R> ex[MODE == M_HOP_CLINV || MODE == M_RECON ? 12 : 1][64];
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+  int base, end, rhs;
+  if (a.slab) {  // uniform
+    const int local = (int)blockIdx.x >> 3, xcd = (int)blockIdx.x & 7;
+    rhs = local % a.nrhs;
+    const int q = local / a.nrhs, ng = (a.g.sT + 63) >> 6;
+    const int n = (((xcd + 1) * ng) >> 3) - ((xcd * ng) >> 3);
+    if (q >= a.t_cnt * n || !slab_group(a.g, xcd, a.t_lo * n + q, base, end)) return;
+  } else {
+    rhs = (int)blockIdx.x % a.nrhs;
+    base = a.t_lo * a.g.sT + ((int)blockIdx.x / a.nrhs) * 64;
+    end = min(base + 64, (a.t_lo + a.t_cnt) * a.g.sT);
+  }
+  const int vh = a.g.Vh;
+  const bool ok = base + lane < end;
+  const int i = ok ? base + lane : end - 1;  // lanes past the end repeat the last site and store nothing
+  const size_t rb = (size_t)rhs * P::SP_E * (size_t)vh * 16;
+  auto vec = [&](const void* p) { return vfield((const char*)p + rb, P::SP_E, vh); };
+  const Nbr nb = neighbours(a.g, decode(a.g, i, a.p_out));
+  const R sf = a.dagger ? R(1) : R(-1), sb = -sf;  // D: forward (1 - g), backward (1 + g)
+  const uint32_t off = voff(i);
+
+  const Field in = vec(a.in);
+  const int jf = w == 0 ? nb.j[0] : w == 1 ? nb.j[2] : w == 2 ? nb.j[4] : nb.j[6];
+  const int jb = w == 0 ? nb.j[1] : w == 1 ? nb.j[3] : w == 2 ? nb.j[5] : nb.j[7];
+  const Spinor<R> pf = P::spinor(in, voff(jf)), pb = P::spinor(in, voff(jb));
+  Link<R> uf, ub;
+  P::links(bfield((const char*)a.links + (size_t)w * P::LK_E * field_vh(vh) * 16, P::LK_E, vh), boff(i, P::LK_E), uf, ub);
+  // the epilogue's own-site vectors: x of both spins of the clover block, b of spin w
+  const int blk = w >> 1;
+  cpx<R> xs[6], bs[3];
+  if constexpr (MODE == M_APPLY || MODE == M_RICH || MODE == M_RESID) {
+    const Field xv = vec(a.x);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) xs[k] = P::row(xv, 6 * blk + k, off);
+  }
+  {
+    Half<R> hf, hb;
+    switch (w) {  // uniform over a wavefront
+      case 0: split_hops<0, R>(pf, pb, uf, ub, sf, sb, nb, hf, hb); break;
+      case 1: split_hops<1, R>(pf, pb, uf, ub, sf, sb, nb, hf, hb); break;
+      case 2: split_hops<2, R>(pf, pb, uf, ub, sf, sb, nb, hf, hb); break;
+      default: split_hops<3, R>(pf, pb, uf, ub, sf, sb, nb, hf, hb); break;
+    }
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      hs[2 * w][k][lane] = hf.c[k / 3][k % 3];
+      hs[2 * w + 1][k][lane] = hb.c[k / 3][k % 3];
+    }
+  }
+  if constexpr (MODE == M_RICH || MODE == M_RESID || MODE == M_RECON || MODE == M_PREP) {
+    const Field bv = vec(a.b);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) bs[c] = P::row(bv, 3 * w + c, off);
+  }
+  cpx<R> sl[18];
+  if constexpr (MODE != M_PREP) P::slots(bfield(a.clov, P::CL_E, vh), boff(i, P::CL_E), blk, sl);
+  // out may be x: both wavefronts of a block have their rows of them before either stores
+  if constexpr (MODE == M_APPLY || MODE == M_RICH || MODE == M_RESID)
+#pragma unroll
+    for (int k = 0; k < 6; ++k) asm volatile("" : "+v"(xs[k].r), "+v"(xs[k].i)::"memory");
+  __syncthreads();
+  cpx<R> h[3] = {{R(0), R(0)}, {R(0), R(0)}, {R(0), R(0)}};
+  switch (w) {
+    case 0: split_sum<0, R>(h, hs, lane, sf, sb); break;
+    case 1: split_sum<1, R>(h, hs, lane, sf, sb); break;
+    case 2: split_sum<2, R>(h, hs, lane, sf, sb); break;
+    default: split_sum<3, R>(h, hs, lane, sf, sb); break;
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) h[c] = R(0.5) * h[c];
+  cpx<R> o[3];
+  if constexpr (MODE == M_PREP) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) o[c] = bs[c] + h[c];
+  } else {
+    cpx<R> v6[6];
+    if constexpr (MODE == M_HOP_CLINV || MODE == M_RECON) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        if constexpr (MODE == M_RECON) h[c] = bs[c] + h[c];
+        ex[3 * w + c][lane] = h[c];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < 6; ++k) v6[k] = ex[6 * blk + k][lane];
+    } else {
+#pragma unroll
+      for (int k = 0; k < 6; ++k) v6[k] = xs[k];
+    }
+    if (w & 1)
+      clover_rows<1, R>(sl, v6, o);
+    else
+      clover_rows<0, R>(sl, v6, o);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const cpx<R> xo = (w & 1) ? v6[3 + c] : v6[c];
+      if constexpr (MODE == M_APPLY) o[c] = o[c] - h[c];
+      if constexpr (MODE == M_RESID) o[c] = bs[c] - o[c] + h[c];
+      if constexpr (MODE == M_RICH) o[c] = xo + (R)a.omega * (bs[c] - o[c] + h[c]);
+    }
+  }
+  if (ok) {
+    const Field out = vec(a.out);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      P::put(out, 3 * w + c, off, o[c]);
+      store_fence();
+    }
+  }
+}
+
+template <class P>
+static hipError_t split_launch(SplitArgs a, int mode, hipStream_t s) {
+  const int ng = (a.g.sT + 63) / 64;
+  if (a.t_cnt <= 0) {
+    a.t_lo = 0;
+    a.t_cnt = a.g.L[3];
+  }
+  a.slab = ng >= 8;  // with fewer groups a slice, slab order leaves XCDs without work
+  const long long grid = a.slab ? 8LL * a.t_cnt * ((ng + 7) / 8) * a.nrhs
+                                : ((long long)a.t_cnt * a.g.sT + 63) / 64 * a.nrhs;
+  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  const dim3 g((unsigned)grid), b(256);
+  constexpr bool WIDE = sizeof(typename P::R) == 8;  // the modes of eq. 2 and the residual run in FP64 only
+  switch (mode) {
+    case M_HOP_CLINV: hipLaunchKernelGGL((hop_split_kernel<P, M_HOP_CLINV>), g, b, 0, s, a); break;
+    case M_APPLY: hipLaunchKernelGGL((hop_split_kernel<P, M_APPLY>), g, b, 0, s, a); break;
+    case M_RICH: hipLaunchKernelGGL((hop_split_kernel<P, M_RICH>), g, b, 0, s, a); break;
+    case M_RECON: if constexpr (WIDE) { hipLaunchKernelGGL((hop_split_kernel<P, M_RECON>), g, b, 0, s, a); break; }
+    case M_RESID: if constexpr (WIDE) { hipLaunchKernelGGL((hop_split_kernel<P, M_RESID>), g, b, 0, s, a); break; }
+    case M_PREP: if constexpr (WIDE) { hipLaunchKernelGGL((hop_split_kernel<P, M_PREP>), g, b, 0, s, a); break; }
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+// Where four threads a site beat one (microseconds a sweep, one thread -> four):
+//   FP64, one right-hand side: latency-bound launches only; 8^4 31 -> 11, 16^4 42 -> 30, but
+//     16^3 x 24 (49,152 sites) 41 -> 42: a workgroup's 61 KB of LDS leave two on a compute unit;
+//   FP32, one: up to 400,000 sites; 8^4 19 -> 9, 16^3 x 32 31 -> 27, 24^3 x 48 (331,776) 142 -> 124,
+//     while 32^4 (524,288) 203 -> 205 (a t-slice's share per XCD has outgrown the sites in flight,
+//     so fewer of them no longer help L2);
+//   several: the wavefronts of one 64-site group follow each other and take links and clover
+//     from L2; FP32 (no tile set) at every size measured, 2 right-hand sides on 32^3 x 64 889 ->
+//     723, 5 on 24^3 x 48 700 -> 487; FP64 from 3 on, 5 on 32^3 x 64 4466 -> 3375, with 2 16^3 x 32
+//     110 -> 90 but 28^3 x 56 890 -> 939;
+//   16 bits: 65,536 sites (16^3 x 32 20 -> 17), 20^3 x 32 (128,000) 25 -> 28; three right-hand
+//     sides 16^4 15 -> 11, 16^3 x 32 16 -> 19 (the one-thread kernel shares a link among three).
+bool hop_split_takes(const Geo& g, int bytes_per_complex, int nrhs) {
+  const long long n = (long long)g.Vh * nrhs;
+  if (bytes_per_complex == 4) return n <= (nrhs == 1 ? 65536 : 98304);
+  if (bytes_per_complex == 8) return nrhs > 1 || n <= 400000;
+  return nrhs > 2 || n <= (nrhs == 1 ? 40960 : 200000);
+}
+
+template <typename R, bool L12>
+static hipError_t split_launch_r(const SplitArgs& a, int mode, hipStream_t s) {
+  // links and clover blocks of both parities, against the 256 MB of the Infinity Cache
+  const long long fields = 2LL * a.g.Vh * ((L12 ? 4 * LINK12_ROWS : 4 * LINK_ROWS) + CLOVER_ROWS) * (long long)sizeof(pair<R>);
+  return fields <= (256LL << 20) ? split_launch<SplitR<R, L12, true>>(a, mode, s) : split_launch<SplitR<R, L12, false>>(a, mode, s);
+}
+
+template <typename R>
+hipError_t launch_hop_split(const HopArgs<R>& h, int mode, bool dagger, int nrhs, hipStream_t s) {
+  SplitArgs a{h.g, h.p_out, h.in, h.links, h.clov, h.x, h.b, h.out, (double)h.omega, nrhs, dagger ? 1 : 0, 0, h.t_lo, h.t_cnt};
+  if (nrhs < 1 || a.t_lo < 0 || a.t_cnt < 0 || a.t_lo + a.t_cnt > a.g.L[3]) return hipErrorInvalidValue;
+  if constexpr (sizeof(R) == 4)
+    if (h.link12) return split_launch_r<float, true>(a, mode, s);
+  return split_launch_r<R, false>(a, mode, s);
+}
+template hipError_t launch_hop_split<double>(const HopArgs<double>&, int, bool, int, hipStream_t);
+template hipError_t launch_hop_split<float>(const HopArgs<float>&, int, bool, int, hipStream_t);
+
+hipError_t launch_hop16_split(int kind, const Hop16Args& h, int mode, hipStream_t s) {
+  const SplitArgs a{h.g, h.p_out, h.in, h.links, h.clov32 ? (const void*)h.clov32 : h.clov, h.x, h.b, h.out, (double)h.omega, h.nrhs, 0, 0, 0, 0};
+  if (h.nrhs < 1) return hipErrorInvalidValue;
+  if (kind == H16_BF16)
+    return h.clov32 ? split_launch<Split16<__bf16, true>>(a, mode, s) : split_launch<Split16<__bf16, false>>(a, mode, s);
+  return h.clov32 ? split_launch<Split16<_Float16, true>>(a, mode, s) : split_launch<Split16<_Float16, false>>(a, mode, s);
+}
+
+}  // namespace ddq
