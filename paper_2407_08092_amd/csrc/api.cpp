@@ -132,8 +132,7 @@ struct ddq_lattice {
   int64_t V, Vh;
   Geo geo;
   hipStream_t stream;
-  // canonical FP64 links kept on the device for the clover build
-  void* U = nullptr;
+  void* U = nullptr;  // staging copy of canonical links that are not read where they are (ddq_set_gauge)
   bool have_gauge = false;
   unsigned store = 0;
   void* links[4][2] = {};  // [prec][parity]; FP16 / BF16 fields are 12-real
@@ -599,7 +598,7 @@ int reserve_impl(ddq_lattice* L) {
       CHK(L->sap_rclov[q].ensure((size_t)CLOVER_ROWS * fvh * 16));
     }
   }
-  if (what & DDQ_RESERVE_FORCE) CHK(L->force_ws.ensure((2 * nv + (size_t)L->V * 54) * 16));
+  if (what & DDQ_RESERVE_FORCE) CHK(L->force_ws.ensure((2 * nv + (size_t)force_insertion_elements(L->geo)) * 16));
   return DDQ_OK;
 }
 
@@ -778,33 +777,30 @@ int ddq_set_gauge(ddq_lattice* L, const void* U, int U_on_device, unsigned stora
   L->have_clover = false;
   L->sap_prec = -1;
   L->sap_res_ok = false;
+  // the links are packed straight from the caller's device array; host links, and a device array
+  // off the 16-byte alignment of the loads, go through the lattice's own copy, which the first
+  // call takes with the other fields so that later ones allocate nothing
   const size_t ubytes = (size_t)L->V * 4 * 9 * 16;
   if (!L->U) CHK(dalloc(&L->U, ubytes));
-  HIPCHK(hipMemcpyAsync(L->U, U, ubytes, U_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
-                        L->stream));
+  const d2_t* Ud = (const d2_t*)U;
+  if (!U_on_device || ((uintptr_t)U & 15)) {
+    HIPCHK(hipMemcpyAsync(L->U, U, ubytes, U_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, L->stream));
+    Ud = (const d2_t*)L->U;
+  }
   const size_t n = (size_t)8 * 9 * field_vh((int)L->Vh);  // complex entries per parity
-  for (int q = 0; q < 2; ++q)
+  const bool f32 = (storage_flags & DDQ_STORE_F32) != 0;
+  L->link12 = (storage_flags & DDQ_STORE_F32_LINK12) != 0;
+  for (int q = 0; q < 2; ++q) {
     if (!L->links[DDQ_F64][q]) {
       CHK(dalloc(&L->links[DDQ_F64][q], n * 16));
       HIPCHK(hipMemsetAsync(L->links[DDQ_F64][q], 0, n * 16, L->stream));  // block padding
     }
-  HIPCHK(launch_pack_gauge_f64(L->geo, (const d2_t*)L->U, (d2_t*)L->links[DDQ_F64][0],
-                               (d2_t*)L->links[DDQ_F64][1], L->stream));
-  L->link12 = (storage_flags & DDQ_STORE_F32_LINK12) != 0;
-  if (storage_flags & DDQ_STORE_F32) {
-    for (int q = 0; q < 2; ++q) {
-      if (!L->links[DDQ_F32][q]) CHK(dalloc(&L->links[DDQ_F32][q], n * 8));
-      if (L->link12)
-        HIPCHK(launch_links_to_f32_12((const d2_t*)L->links[DDQ_F64][q], L->links[DDQ_F32][q], (int)L->Vh,
-                                      L->stream));
-      else
-        HIPCHK(launch_field_to_f32((const d2_t*)L->links[DDQ_F64][q], L->links[DDQ_F32][q], 4, LINK_ROWS,
-                                   (int)L->Vh, L->stream));
-    }
-  } else {
-    for (int q = 0; q < 2; ++q) dfree(L->links[DDQ_F32][q]);
-    L->h16_clover32 = false;  // no FP32 clover blocks without FP32 storage
+    if (f32 && !L->links[DDQ_F32][q]) CHK(dalloc(&L->links[DDQ_F32][q], n * 8));
+    if (!f32) dfree(L->links[DDQ_F32][q]);
   }
+  if (!f32) L->h16_clover32 = false;  // no FP32 clover blocks without FP32 storage
+  HIPCHK(launch_pack_gauge(L->geo, Ud, (d2_t*)L->links[DDQ_F64][0], (d2_t*)L->links[DDQ_F64][1], L->links[DDQ_F32][0],
+                           L->links[DDQ_F32][1], L->link12 ? 1 : 0, L->stream));
   // 16-bit storage: 12-real links, 3 element rows per direction
   const size_t n16 = (size_t)4 * 3 * field_vh((int)L->Vh) * 16;
   for (int prec : {DDQ_F16, DDQ_BF16}) {
@@ -847,20 +843,20 @@ int ddq_set_clover(ddq_lattice* L, double c_sw, double m0) {
     CHK(dalloc(&L->clov_oo, n * 16));
     HIPCHK(hipMemsetAsync(L->clov_oo, 0, n * 16, L->stream));
   }
-  int* flag = (int*)L->small.p;
-  HIPCHK(hipMemsetAsync(flag, 0, sizeof(int), L->stream));
-  HIPCHK(launch_clover_build(L->geo, (const d2_t*)L->U, c_sw, m0, (d2_t*)L->clov[DDQ_F64][0],
-                             (d2_t*)L->clov[DDQ_F64][1], (d2_t*)L->clov_oo, flag, L->stream));
-  CHK(fetch(L, flag, sizeof(int)));
-  int notpd = ((int*)L->host)[0];
-  if (notpd) return fail(DDQ_ERR_NOT_PD, "a 6x6 clover block is not positive definite");
-  if (L->links[DDQ_F32][0]) {
-    for (int q = 0; q < 2; ++q) {
+  const bool f32 = L->links[DDQ_F32][0] != nullptr;
+  if (f32)
+    for (int q = 0; q < 2; ++q)
       if (!L->clov[DDQ_F32][q]) CHK(dalloc(&L->clov[DDQ_F32][q], n * 8));
-      HIPCHK(launch_field_to_f32((const d2_t*)L->clov[DDQ_F64][q], L->clov[DDQ_F32][q], 1, CLOVER_ROWS,
-                                 (int)L->Vh, L->stream));
-    }
-  }
+  const ClovOut out{(d2_t*)L->clov[DDQ_F64][0], (d2_t*)L->clov[DDQ_F64][1], (d2_t*)L->clov_oo,
+                    f32 ? L->clov[DDQ_F32][0] : nullptr, f32 ? L->clov[DDQ_F32][1] : nullptr};
+  // the flag lives in the pinned host buffer: no copy of it in either direction
+  CHK(ensure_host(L, sizeof(int)));
+  volatile int* flag = (volatile int*)L->host;
+  *flag = 0;
+  HIPCHK(launch_clover_build(L->geo, (const d2_t*)L->links[DDQ_F64][0], (const d2_t*)L->links[DDQ_F64][1], c_sw, m0, out,
+                             (int*)L->host, L->stream));
+  HIPCHK(hipStreamSynchronize(L->stream));
+  if (*flag) return fail(DDQ_ERR_NOT_PD, "a 6x6 clover block is not positive definite");
   const size_t n16 = (size_t)10 * field_vh((int)L->Vh) * 16;  // 16-bit: 10 element rows
   for (int prec : {DDQ_F16, DDQ_BF16}) {
     if (!L->links[prec][0]) continue;
@@ -1333,7 +1329,7 @@ int ddq_backward_link_force(ddq_lattice* L, const void* chi_e, const void* phi_e
   if (!chi_e || !phi_e) return fail(DDQ_ERR_ARG, "chi_e and phi_e must be non-null");
   if (!G && !F) return DDQ_OK;
   const long long n = L->nvec();
-  const size_t need = (size_t)(2 * n + L->V * 54) * 16;
+  const size_t need = (size_t)(2 * n + force_insertion_elements(L->geo)) * 16;
   CHK(L->force_ws.ensure(need));
   CHK(ensure_tmp(L, DDQ_F64, 1));
   d2_t* psi = (d2_t*)L->force_ws.p;
@@ -1342,7 +1338,7 @@ int ddq_backward_link_force(ddq_lattice* L, const void* chi_e, const void* phi_e
   // psi_o = A_oo^-1 H_oe phi_e ;  lambda_o = A_oo^-1 (H^H)_oe chi_e  (kernel A, plain and dagger)
   HIPCHK(kernel_A<double>(L, DDQ_F64, 1, (const d2_t*)phi_e, psi, false));
   HIPCHK(kernel_A<double>(L, DDQ_F64, 1, (const d2_t*)chi_e, lam, true));
-  HIPCHK(launch_force(L->geo, (const d2_t*)L->U, (const d2_t*)chi_e, lam, (const d2_t*)phi_e, psi, L->c_sw, W,
+  HIPCHK(launch_force(L->geo, (const d2_t*)L->links[DDQ_F64][0], (const d2_t*)L->links[DDQ_F64][1], (const d2_t*)chi_e, lam, (const d2_t*)phi_e, psi, L->c_sw, W,
                       (d2_t*)G, (double*)F, accumulate, L->stream));
   return DDQ_OK;
 }

@@ -244,16 +244,18 @@ hipError_t launch_norm2_b(const d2_t* w, long long n, int nrhs, double* partial,
 hipError_t launch_scale_b(d2_t* out, const d2_t* in, const double* f, long long n, int nrhs, hipStream_t s);
 hipError_t launch_inv_norm_b(const double* hn, double* f, int nrhs, double tiny2, hipStream_t s);
 
-// link force: insertions W (V x 54 complex) then per-link G (V x 4 x 9 complex) / F (V x 4 x 8)
-hipError_t launch_force(const Geo& g, const d2_t* U, const d2_t* chi_e, const d2_t* lam_o, const d2_t* phi_e,
-                        const d2_t* psi_o, double c_sw, d2_t* W, d2_t* G, double* F, int accumulate,
+// link force: insertions W (force_insertion_elements 16-byte elements) then per-link G (V x 4 x 9
+// complex) / F (V x 4 x 8)
+long long force_insertion_elements(const Geo& g);
+hipError_t launch_force(const Geo& g, const d2_t* links_e, const d2_t* links_o, const d2_t* chi_e, const d2_t* lam_o,
+                        const d2_t* phi_e, const d2_t* psi_o, double c_sw, d2_t* W, d2_t* G, double* F, int accumulate,
                         hipStream_t s);
 
 // field kernels
-hipError_t launch_pack_gauge_f64(const Geo& g, const d2_t* U, d2_t* out_even, d2_t* out_odd,
-                                 hipStream_t s);
-hipError_t launch_field_to_f32(const d2_t* in, void* out, int nfields, int crows, int vh, hipStream_t s);
-hipError_t launch_links_to_f32_12(const d2_t* in, void* out, int vh, hipStream_t s);
+// FP64 link fields of both parities from canonical links and, unless null, the FP32 ones
+// (12-real: link12)
+hipError_t launch_pack_gauge(const Geo& g, const d2_t* U, d2_t* out_even, d2_t* out_odd, void* f32_even, void* f32_odd,
+                             int link12, hipStream_t s);
 hipError_t launch_parity_to_f32(void* y, const d2_t* x, int nrhs, int vh, hipStream_t s);
 hipError_t launch_parity_to_f64(d2_t* y, const void* x, int nrhs, int vh, hipStream_t s);
 // sources of the SAP residual r = b - D x (FP64 full vectors b, x; FP64 links per parity
@@ -280,9 +282,15 @@ hipError_t launch_sap_residual(const Geo& g, const SapResidualSrc& src, d2_t* r,
 // 128 sites of that parity of every 4^4 block consecutive), as launch_sap_blocks reads
 // its links and clover
 hipError_t launch_sap_reorder(const Geo& g, int parity, const void* src, void* dst, int erows, hipStream_t s);
-// A_ee into clov_even, A_oo^-1 into clov_odd_inv and (when not null) A_oo into clov_odd
-hipError_t launch_clover_build(const Geo& g, const d2_t* U, double c_sw, double m0,
-                               d2_t* clov_even, d2_t* clov_odd_inv, d2_t* clov_odd, int* notpd, hipStream_t s);
+// clover fields from the packed links: A_ee, A_oo^-1, A_oo and, unless null, FP32 copies of the
+// first two; *notpd (zero before; host memory the device can write) becomes 1 where a block of an
+// odd site is not positive definite
+struct ClovOut {
+  d2_t *e, *o_inv, *o;
+  void *e32, *o_inv32;
+};
+hipError_t launch_clover_build(const Geo& g, const d2_t* links_even, const d2_t* links_odd, double c_sw, double m0,
+                               const ClovOut& out, int* notpd, hipStream_t s);
 hipError_t launch_clover_export(const Geo& g, const d2_t* packed, d2_t* dense, hipStream_t s);
 template <typename R>
 hipError_t launch_pack_parity(const Geo& g, int parity, int nrhs, const pair<R>* full, pair<R>* v,

@@ -1,6 +1,6 @@
 // fields.hip -- set-up kernels: gauge packing, clover blocks and their inverses,
 // parity packing of vectors.
-#include "ddq_internal.h"
+#include "gauge_common.h"
 
 namespace ddq {
 
@@ -9,353 +9,311 @@ __device__ __forceinline__ long long lex(const Geo& g, int x, int y, int z, int 
   return x + (long long)g.L[0] * (y + (long long)g.L[1] * (z + (long long)g.L[2] * t));
 }
 
-__device__ __forceinline__ void coords_shift(const Geo& g, int c[4], int mu, int step) {
-  c[mu] += step;
-  if (c[mu] < 0) c[mu] += g.L[mu];
-  if (c[mu] >= g.L[mu]) c[mu] -= g.L[mu];
-}
-
 // ---------------------------------------------------------------------------
 // gauge packing: per parity p, direction mu and site i, complex rows 0..8 = U_mu(x)
-// and rows 9..17 = U_mu(x-mu)^H (FP64: one complex per 16-byte element)
+// and rows 9..17 = U_mu(x-mu)^H (FP64: one complex per 16-byte element), and in the same
+// pass the FP32 copy (18- or 12-real).
+//
+// A pass over memory: 576 B a site read, 2304 B (FP64) and 1152 or 768 B (FP32) written.  A
+// workgroup takes the 128 consecutive sites of one 64-site block of both parities, a wavefront
+// one direction of them: it reads their links in runs of 144 B into LDS and writes rows of 64
+// sites, each link twice -- forward at its own site, daggered at x + mu, whose index runs with
+// the lane.  16^3 x 32 with FP32: 51 us (5.9 TB/s) from 180
+// in a copy, a pass that read 16-byte elements 576 B apart, and four conversions.
 // ---------------------------------------------------------------------------
-__global__ void k_pack_gauge(Geo g, const d2_t* __restrict__ U, d2_t* __restrict__ out_e,
-                             d2_t* __restrict__ out_o) {
+constexpr int PACK_SITES = 128;
+
+// rows [r0, r0 + 9) of one site in the FP32 field of direction mu
+__device__ __forceinline__ void put_link_f32(f2_t* f, int mu, int r0, int i, int vh, int mode, const cpx<double> (&u)[9]) {
+  const size_t fv = (size_t)field_vh(vh);
+  auto two = [&](int k) {
+    f4_t o;
+    o.x = (float)u[k].r;
+    o.y = (float)u[k].i;
+    o.z = (float)u[k + 1].r;
+    o.w = (float)u[k + 1].i;
+    return o;
+  };
+  if (mode == 12) {  // rows 0..5 of each half: elements 0..2 and 3..5
+    constexpr int ER = LINK12_ROWS / 2;
+    f4_t* d = (f4_t*)f + (size_t)mu * ER * fv;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) d[fidx((r0 ? 3 : 0) + e, i, ER, vh)] = two(2 * e);
+    return;
+  }
+  constexpr int ER = LINK_ROWS / 2;
+  f4_t* d = (f4_t*)f + (size_t)mu * ER * fv;
+  f2_t one;  // rows 8 and 9 share element 4
+  const int k1 = r0 ? 0 : 8;
+  one.x = (float)u[k1].r;
+  one.y = (float)u[k1].i;
+  ((f2_t*)&d[fidx(4, i, ER, vh)])[r0 ? 1 : 0] = one;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) d[fidx(r0 ? 5 + e : e, i, ER, vh)] = two(r0 ? 2 * e + 1 : 2 * e);
+}
+
+__global__ void __launch_bounds__(256) k_pack_gauge(Geo g, const d2_t* __restrict__ U, d2_t* __restrict__ out_e,
+                                                    d2_t* __restrict__ out_o, f2_t* __restrict__ f32_e,
+                                                    f2_t* __restrict__ f32_o, int f32_mode) {
+  __shared__ d2_t lds[4][PACK_SITES * 9];
+  const int mu = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
   const int vh = g.Vh;
-  long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid >= 2LL * vh) return;
-  const int p = (int)(tid / vh);
-  const int i = (int)(tid % vh);
-  Site s = decode(g, i, p);
-  d2_t* out = p == 0 ? out_e : out_o;
-  const long long n = lex(g, s.x, s.y, s.z, s.t);
+  const long long n0 = (long long)blockIdx.x * PACK_SITES;
+  const int sites = (int)min((long long)PACK_SITES, 2LL * vh - n0);
+  d2_t* l = lds[mu];
+#pragma unroll
+  for (int k = 0; k < PACK_SITES * 9 / 64; ++k) {
+    const int q = 64 * k + lane, s = q / 9, e = q - 9 * s;
+    if (s < sites) l[q] = U[((n0 + s) * 4 + mu) * 9 + e];
+  }
+  __syncthreads();
+  const int i = (int)(n0 >> 1) + lane;
+  if (i >= vh) return;
   const size_t fsz = (size_t)LINK_ROWS * field_vh(vh);  // one direction's link field
-  for (int mu = 0; mu < 4; ++mu) {
-    const d2_t* u = U + (n * 4 + mu) * 9;
-    for (int e = 0; e < 9; ++e) {
-      out[mu * fsz + fidx(e, i, LINK_ROWS, vh)] = u[e];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const Site s = decode(g, i, p);
+    const d2_t* src = l + (2 * lane + (s.x & 1)) * 9;
+    cpx<double> u[9], d[9];
+#pragma unroll
+    for (int e = 0; e < 9; ++e) u[e] = {src[e].x, src[e].y};
+    d2_t* fwd = (p ? out_o : out_e) + mu * fsz;
+#pragma unroll
+    for (int e = 0; e < 9; ++e) fwd[fidx(e, i, LINK_ROWS, vh)] = d2_t{u[e].r, u[e].i};
+    store_fence();
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) d[3 * a + b] = conj(u[3 * b + a]);
+    const int j = site_shift(g, s, mu, 1).i;  // the link is the backward one of x + mu
+    d2_t* bwd = (p ? out_e : out_o) + mu * fsz;
+#pragma unroll
+    for (int e = 0; e < 9; ++e) bwd[fidx(9 + e, j, LINK_ROWS, vh)] = d2_t{d[e].r, d[e].i};
+    store_fence();
+    if (f32_mode) {  // uniform
+      put_link_f32(p ? f32_o : f32_e, mu, 0, i, vh, f32_mode, u);
+      store_fence();
+      put_link_f32(p ? f32_e : f32_o, mu, 9, j, vh, f32_mode, d);
       store_fence();
     }
-    int c[4] = {s.x, s.y, s.z, s.t};
-    coords_shift(g, c, mu, -1);
-    const long long nb = lex(g, c[0], c[1], c[2], c[3]);
-    const d2_t* ub = U + (nb * 4 + mu) * 9;
-    for (int a = 0; a < 3; ++a)
-      for (int b = 0; b < 3; ++b) {
-        d2_t v = ub[3 * b + a];
-        v.y = -v.y;
-        out[mu * fsz + fidx(9 + 3 * a + b, i, LINK_ROWS, vh)] = v;
-        store_fence();
-      }
   }
 }
 
-hipError_t launch_pack_gauge_f64(const Geo& g, const d2_t* U, d2_t* out_e, d2_t* out_o, hipStream_t s) {
-  long long n = 2LL * g.Vh;
-  int blocks = (int)((n + 255) / 256);
-  hipLaunchKernelGGL(k_pack_gauge, dim3(blocks), dim3(256), 0, s, g, U, out_e, out_o);
-  return hipGetLastError();
-}
-
-// FP64 blocked fields (nfields fields of crows complex rows) -> FP32 blocked fields
-// whose 16-byte element e holds complex rows 2e and 2e+1
-__global__ void k_field_to_f32(const d2_t* __restrict__ in, f4_t* __restrict__ out, int nfields, int crows, int vh) {
-  const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int er = crows / 2;
-  const long long total = (long long)nfields * er * vh;
-  if (tid >= total) return;
-  const int i = (int)(tid % vh);
-  const int e = (int)((tid / vh) % er);
-  const int f = (int)(tid / ((long long)vh * er));
-  const size_t fv = (size_t)field_vh(vh);
-  const d2_t* src = in + (size_t)f * crows * fv;
-  d2_t a = src[fidx(2 * e, i, crows, vh)], b = src[fidx(2 * e + 1, i, crows, vh)];
-  f4_t o;
-  o.x = (float)a.x;
-  o.y = (float)a.y;
-  o.z = (float)b.x;
-  o.w = (float)b.y;
-  out[(size_t)f * er * fv + fidx(e, i, er, vh)] = o;
-}
-
-// FP64 link fields (4 directions x LINK_ROWS) -> FP32 12-real link fields: complex
-// rows 0..5 (first two rows of U_mu(x)) and 9..14 (of U_mu(x - mu)^H), paired
-__global__ void k_links_to_f32_12(const d2_t* __restrict__ in, f4_t* __restrict__ out, int vh) {
-  const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int er = LINK12_ROWS / 2;
-  if (tid >= 4LL * er * vh) return;
-  const int i = (int)(tid % vh);
-  const int e = (int)((tid / vh) % er);
-  const int mu = (int)(tid / ((long long)vh * er));
-  const size_t fv = (size_t)field_vh(vh);
-  const d2_t* src = in + (size_t)mu * LINK_ROWS * fv;
-  auto row = [](int k) { return k < 6 ? k : k + 3; };  // 12-real row -> 18-entry row
-  d2_t a = src[fidx(row(2 * e), i, LINK_ROWS, vh)], b = src[fidx(row(2 * e + 1), i, LINK_ROWS, vh)];
-  f4_t o;
-  o.x = (float)a.x;
-  o.y = (float)a.y;
-  o.z = (float)b.x;
-  o.w = (float)b.y;
-  out[(size_t)mu * er * fv + fidx(e, i, er, vh)] = o;
-}
-
-hipError_t launch_links_to_f32_12(const d2_t* in, void* out, int vh, hipStream_t s) {
-  const long long total = 4LL * (LINK12_ROWS / 2) * vh;
-  hipLaunchKernelGGL(k_links_to_f32_12, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, in, (f4_t*)out, vh);
-  return hipGetLastError();
-}
-
-hipError_t launch_field_to_f32(const d2_t* in, void* out, int nfields, int crows, int vh, hipStream_t s) {
-  const long long total = (long long)nfields * (crows / 2) * vh;
-  hipLaunchKernelGGL(k_field_to_f32, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, in, (f4_t*)out,
-                     nfields, crows, vh);
+hipError_t launch_pack_gauge(const Geo& g, const d2_t* U, d2_t* out_e, d2_t* out_o, void* f32_e, void* f32_o, int link12,
+                             hipStream_t s) {
+  const long long blocks = (2LL * g.Vh + PACK_SITES - 1) / PACK_SITES;
+  hipLaunchKernelGGL(k_pack_gauge, dim3((unsigned)blocks), dim3(256), 0, s, g, U, out_e, out_o, (f2_t*)f32_e, (f2_t*)f32_o,
+                     f32_e ? (link12 ? 12 : 18) : 0);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
 // clover blocks
 // ---------------------------------------------------------------------------
-struct M3 {
-  cpx<double> a[3][3];
-};
-
-__device__ __forceinline__ M3 load_link(const Geo& g, const d2_t* U, const int c[4], int mu) {
-  const long long n = lex(g, c[0], c[1], c[2], c[3]);
-  const d2_t* u = U + (n * 4 + mu) * 9;
-  M3 m;
+// F_munu(x) of plane (mu, nu) from Q = the four leaves, F = (Q - Q^H) / 8.  With
+//   S = U_nu(x+mu) U_mu(x+nu)^H U_nu(x)^H - U_nu(x+mu-nu)^H U_mu(x-nu)^H U_nu(x-nu),
+//   X = U_nu(x) U_mu(x-mu+nu)^H U_nu(x-mu)^H - U_nu(x-nu)^H U_mu(x-mu-nu)^H U_nu(x-mu-nu)
+// the leaves 1 and 4 are U_mu(x) S and leaves 2 and 3 X U_mu(x-mu), up to Hermitian
+// conjugates that Q - Q^H cancels: Q - Q^H = T - T^H, T = U_mu(x) S + X U_mu(x-mu).
+__device__ __forceinline__ AH3 field_strength(const PackedLinks& L, const Geo& g, const Site& s, int p, int mu, int nu) {
+  const int o = 1 - p;
+  const Site fm = site_shift(g, s, mu, 1), fn = site_shift(g, s, nu, 1);
+  const Site bm = site_shift(g, s, mu, -1), bn = site_shift(g, s, nu, -1);
+  auto U = [&](int q, int dir, int i) { return packed_link(L, g, q, dir, i); };
+  // one product at a time (c3_fence): the matrices in flight fit the registers of three wavefronts
+  C3 A = c3_mul_dag(U(o, nu, fm.i), U(o, mu, fn.i));
+  c3_fence(A);
+  C3 S = c3_mul_dag(A, U(p, nu, s.i));
+  c3_fence(S);
+  A = c3_mul(U(o, mu, bn.i), U(p, nu, site_shift(g, fm, nu, -1).i));
+  c3_fence(A);
+  S = c3_sub(S, c3_dag_mul(A, U(o, nu, bn.i)));
+  c3_fence(S);
+  C3 T = c3_mul(U(p, mu, s.i), S);
+  c3_fence(T);
+  A = c3_mul_dag(U(p, nu, s.i), U(p, mu, site_shift(g, fn, mu, -1).i));
+  c3_fence(A);
+  S = c3_mul_dag(A, U(o, nu, bm.i));
+  c3_fence(S);
+  const int bb = site_shift(g, bm, nu, -1).i;  // x-mu-nu
+  A = c3_mul(U(p, mu, bb), U(o, nu, bn.i));
+  c3_fence(A);
+  S = c3_sub(S, c3_dag_mul(A, U(p, nu, bb)));
+  c3_fence(S);
+  T = c3_add(T, c3_mul(S, U(o, mu, bm.i)));
+  AH3 F;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) F.d[a] = 0.25 * T.a[a][a].i;
+#pragma unroll
   for (int a = 0; a < 3; ++a)
-    for (int b = 0; b < 3; ++b) {
-      d2_t v = u[3 * a + b];
-      m.a[a][b] = {v.x, v.y};
-    }
-  return m;
-}
-
-__device__ __forceinline__ M3 mul(const M3& A, const M3& B) {
-  M3 C;
-  for (int a = 0; a < 3; ++a)
-    for (int b = 0; b < 3; ++b) {
-      cpx<double> s = A.a[a][0] * B.a[0][b];
-      cfma(s, A.a[a][1], B.a[1][b]);
-      cfma(s, A.a[a][2], B.a[2][b]);
-      C.a[a][b] = s;
-    }
-  return C;
-}
-
-__device__ __forceinline__ M3 dagger(const M3& A) {
-  M3 C;
-  for (int a = 0; a < 3; ++a)
-    for (int b = 0; b < 3; ++b) C.a[a][b] = conj(A.a[b][a]);
-  return C;
-}
-
-// Q_munu(x): the four counter-clockwise leaves of the mu-nu plane that touch x
-__device__ M3 clover_leaves(const Geo& g, const d2_t* U, const int x[4], int mu, int nu) {
-  int c[4];
-  M3 Q;
-  // leaf 1: U_mu(x) U_nu(x+mu) U_mu(x+nu)^H U_nu(x)^H
-  {
-    M3 a = load_link(g, U, x, mu);
-    for (int k = 0; k < 4; ++k) c[k] = x[k];
-    coords_shift(g, c, mu, 1);
-    M3 b = load_link(g, U, c, nu);
-    for (int k = 0; k < 4; ++k) c[k] = x[k];
-    coords_shift(g, c, nu, 1);
-    M3 d = dagger(load_link(g, U, c, mu));
-    M3 e = dagger(load_link(g, U, x, nu));
-    Q = mul(mul(mul(a, b), d), e);
-  }
-  // leaf 2: U_nu(x) U_mu(x-mu+nu)^H U_nu(x-mu)^H U_mu(x-mu)
-  {
-    M3 a = load_link(g, U, x, nu);
-    for (int k = 0; k < 4; ++k) c[k] = x[k];
-    coords_shift(g, c, mu, -1);
-    coords_shift(g, c, nu, 1);
-    M3 b = dagger(load_link(g, U, c, mu));
-    for (int k = 0; k < 4; ++k) c[k] = x[k];
-    coords_shift(g, c, mu, -1);
-    M3 d = dagger(load_link(g, U, c, nu));
-    M3 e = load_link(g, U, c, mu);
-    M3 L = mul(mul(mul(a, b), d), e);
-    for (int i = 0; i < 3; ++i)
-      for (int j = 0; j < 3; ++j) Q.a[i][j] = Q.a[i][j] + L.a[i][j];
-  }
-  // leaf 3: U_mu(x-mu)^H U_nu(x-mu-nu)^H U_mu(x-mu-nu) U_nu(x-nu)
-  {
-    for (int k = 0; k < 4; ++k) c[k] = x[k];
-    coords_shift(g, c, mu, -1);
-    M3 a = dagger(load_link(g, U, c, mu));
-    coords_shift(g, c, nu, -1);
-    M3 b = dagger(load_link(g, U, c, nu));
-    M3 d = load_link(g, U, c, mu);
-    for (int k = 0; k < 4; ++k) c[k] = x[k];
-    coords_shift(g, c, nu, -1);
-    M3 e = load_link(g, U, c, nu);
-    M3 L = mul(mul(mul(a, b), d), e);
-    for (int i = 0; i < 3; ++i)
-      for (int j = 0; j < 3; ++j) Q.a[i][j] = Q.a[i][j] + L.a[i][j];
-  }
-  // leaf 4: U_nu(x-nu)^H U_mu(x-nu) U_nu(x+mu-nu) U_mu(x)^H
-  {
-    for (int k = 0; k < 4; ++k) c[k] = x[k];
-    coords_shift(g, c, nu, -1);
-    M3 a = dagger(load_link(g, U, c, nu));
-    M3 b = load_link(g, U, c, mu);
-    coords_shift(g, c, mu, 1);
-    M3 d = load_link(g, U, c, nu);
-    M3 e = dagger(load_link(g, U, x, mu));
-    M3 L = mul(mul(mul(a, b), d), e);
-    for (int i = 0; i < 3; ++i)
-      for (int j = 0; j < 3; ++j) Q.a[i][j] = Q.a[i][j] + L.a[i][j];
-  }
-  return Q;
-}
-
-// F = (Q - Q^H) / 8
-__device__ __forceinline__ M3 field_from_leaves(const M3& Q) {
-  M3 F;
-  for (int a = 0; a < 3; ++a)
-    for (int b = 0; b < 3; ++b) {
-      cpx<double> q = Q.a[a][b], qt = conj(Q.a[b][a]);
-      F.a[a][b] = {(q.r - qt.r) * 0.125, (q.i - qt.i) * 0.125};
-    }
+#pragma unroll
+    for (int b = a + 1; b < 3; ++b)
+      F.u[a + b - 1] = {0.125 * (T.a[a][b].r - T.a[b][a].r), 0.125 * (T.a[a][b].i + T.a[b][a].i)};
   return F;
 }
 
-// write a Hermitian 6x6 block (full matrix M) into the packed 18-slot format
-// block blk of site i of a 36-row clover field
-__device__ __forceinline__ void store_packed(d2_t* C, int blk, int i, int vh, const cpx<double> M[6][6]) {
-  for (int k = 0; k < 3; ++k) {
-    d2_t v;
-    v.x = M[2 * k][2 * k].r;
-    v.y = M[2 * k + 1][2 * k + 1].r;
-    C[fidx(18 * blk + k, i, 36, vh)] = v;
-    store_fence();
-  }
+// slots of a Hermitian 6x6 block (upper triangle and diagonal of M) into block blk of site i of
+// a clover field of R (FP32: two slots per 16-byte element)
+template <typename R>
+__device__ __forceinline__ void store_packed(void* C, int blk, int i, int vh, const cpx<double> (&M)[6][6]) {
+  constexpr int E = 18 / CPE<R>;  // elements of a block
+  const Field f = bfield(C, 2 * E, vh);
+  const uint32_t off = boff(i, 2 * E);
+  cpx<R> sl[18];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) sl[k] = {(R)M[2 * k][2 * k].r, (R)M[2 * k + 1][2 * k + 1].r};
+#pragma unroll
   for (int j = 0; j < 6; ++j)
-    for (int k = j + 1; k < 6; ++k) {
-      d2_t v;
-      v.x = M[j][k].r;
-      v.y = M[j][k].i;
-      C[fidx(18 * blk + tri_slot(j, k), i, 36, vh)] = v;
-      store_fence();
-    }
+#pragma unroll
+    for (int k = j + 1; k < 6; ++k) sl[tri_slot(j, k)] = {(R)M[j][k].r, (R)M[j][k].i};
+#pragma unroll
+  for (int e = 0; e < E; ++e) st16<0>(f, E * blk + e, off, pack<R>(sl + e * CPE<R>));
 }
 
-// In-place inverse of a Hermitian positive-definite 6x6 matrix by Cholesky
-// A = L L^H; returns false if a pivot is not positive.
-__device__ bool hpd_inverse6(cpx<double> A[6][6]) {
-  cpx<double> L[6][6];
-  for (int j = 0; j < 6; ++j)
-    for (int k = 0; k < 6; ++k) L[j][k] = {0.0, 0.0};
+// Inverse of a Hermitian positive-definite 6x6 matrix by Cholesky A = L L^H: reads and writes A's
+// diagonal and upper triangle, L, L^-1 and the products in place below it; returns false if a
+// pivot is not positive.
+__device__ __forceinline__ bool hpd_inverse6(cpx<double> (&A)[6][6]) {
+  bool ok = true;
+  double inv[6];  // 1 / L_jj
+#pragma unroll
   for (int j = 0; j < 6; ++j) {
     double d = A[j][j].r;
-    for (int k = 0; k < j; ++k) d -= L[j][k].r * L[j][k].r + L[j][k].i * L[j][k].i;
-    if (!(d > 0.0)) return false;
-    double ljj = sqrt(d);
-    L[j][j] = {ljj, 0.0};
+#pragma unroll
+    for (int k = 0; k < j; ++k) d -= A[j][k].r * A[j][k].r + A[j][k].i * A[j][k].i;
+    if (!(d > 0.0)) {
+      ok = false;
+      d = 1.0;
+    }
+    inv[j] = 1.0 / sqrt(d);
+#pragma unroll
     for (int r = j + 1; r < 6; ++r) {
-      cpx<double> s = A[r][j];
-      for (int k = 0; k < j; ++k) {
-        cpx<double> t = L[r][k] * conj(L[j][k]);
-        s = s - t;
-      }
-      L[r][j] = {s.r / ljj, s.i / ljj};
+      cpx<double> s = conj(A[j][r]);
+#pragma unroll
+      for (int k = 0; k < j; ++k) s = s - A[r][k] * conj(A[j][k]);
+      A[r][j] = inv[j] * s;
     }
+    __builtin_amdgcn_sched_barrier(0);
   }
-  // Linv = L^-1 (lower triangular), column by column by forward substitution
-  cpx<double> Li[6][6];
-  for (int j = 0; j < 6; ++j)
-    for (int k = 0; k < 6; ++k) Li[j][k] = {0.0, 0.0};
-  for (int c = 0; c < 6; ++c) {
-    Li[c][c] = {1.0 / L[c][c].r, 0.0};
-    for (int r = c + 1; r < 6; ++r) {
-      cpx<double> s = {0.0, 0.0};
-      for (int k = c; k < r; ++k) cfma(s, L[r][k], Li[k][c]);
-      Li[r][c] = {-s.r / L[r][r].r, -s.i / L[r][r].r};
+  // L^-1 below the diagonal, column by column from the last: column c from L^-1's rows and columns > c
+#pragma unroll
+  for (int c = 4; c >= 0; --c) {
+#pragma unroll
+    for (int r = 5; r > c; --r) {
+      cpx<double> s = inv[r] * A[r][c];
+#pragma unroll
+      for (int k = c + 1; k < r; ++k) cfma(s, A[r][k], A[k][c]);
+      A[r][c] = {-s.r * inv[c], -s.i * inv[c]};
     }
+    __builtin_amdgcn_sched_barrier(0);
   }
-  // A^-1 = Li^H Li
-  for (int j = 0; j < 6; ++j)
-    for (int k = 0; k < 6; ++k) {
-      cpx<double> s = {0.0, 0.0};
-      for (int r = (j > k ? j : k); r < 6; ++r) cfma_conj(s, Li[r][j], Li[r][k]);
+  // A^-1 = (L^-1)^H L^-1
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    double d = inv[j] * inv[j];
+#pragma unroll
+    for (int r = j + 1; r < 6; ++r) d = fma(A[r][j].r, A[r][j].r, fma(A[r][j].i, A[r][j].i, d));
+    A[j][j] = {d, 0.0};
+#pragma unroll
+    for (int k = j + 1; k < 6; ++k) {
+      cpx<double> s = inv[k] * conj(A[k][j]);
+#pragma unroll
+      for (int r = k + 1; r < 6; ++r) cfma_conj(s, A[r][j], A[r][k]);
       A[j][k] = s;
     }
-  return true;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  return ok;
 }
 
 // Per site: A_+- = (4 + m0) 1_6 + (i c_sw / 2) sum_l s_l (x) E_l^+-,
 // E_l^+- = +-F_{l t} - F_{jk}, (l, j, k) cyclic over (x, y, z).  This is the
 // chiral-basis form of (4 + m0) + (i c_sw / 4) sum sigma_munu F_munu:
 // sigma_{l t} = diag(s_l, -s_l) and sigma_{jk} = -diag(s_l, s_l).
-__global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) k_clover_build(Geo g, const d2_t* __restrict__ U, double c_sw, double m0,
-                               d2_t* __restrict__ cl_e, d2_t* __restrict__ cl_o_inv,
-                               d2_t* __restrict__ cl_o, int* notpd) {
+//
+// A workgroup is 64 sites of one parity x 6 wavefronts, one per plane; the six F meet in LDS,
+// from which two wavefronts (one per block) form, and on odd sites invert, the 6x6 blocks.
+// Bound by the latency of the links (one product at a time, three wavefronts a SIMD): 16^3 x 32
+// 225 us (one thread a site on canonical links, 464 B of scratch, and 2 x 17 us for the FP32 copy)
+// -> 96.  Few sites in flight matter more than registers: four wavefronts with three planes each
+// of both parities read 506 MB past L2 against 165 here, and took the same 93 us with twice the
+// matrices in flight.
+constexpr int CLOVER_PLANES = 6;
+__global__ void __launch_bounds__(64 * CLOVER_PLANES) __attribute__((amdgpu_waves_per_eu(3)))
+k_clover_build(Geo g, PackedLinks L, double c_sw, double m0, ClovOut out, int* notpd) {
+  __shared__ double Fs[CLOVER_PLANES][9][64];
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+  int p, base, end;
+  if (!gauge_group(g, (int)blockIdx.x, 2, p, base, end)) return;
   const int vh = g.Vh;
-  long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid >= 2LL * vh) return;
-  const int p = (int)(tid / vh);
-  const int i = (int)(tid % vh);
-  Site s = decode(g, i, p);
-  const int x[4] = {s.x, s.y, s.z, s.t};
-  // the six F_munu, indexed by (mu, nu) with mu < nu
-  M3 Fxt = field_from_leaves(clover_leaves(g, U, x, 0, 3));
-  M3 Fyt = field_from_leaves(clover_leaves(g, U, x, 1, 3));
-  M3 Fzt = field_from_leaves(clover_leaves(g, U, x, 2, 3));
-  M3 Fyz = field_from_leaves(clover_leaves(g, U, x, 1, 2));
-  M3 Fzx;  // F_zx = -F_xz
+  const bool in = base + lane < end;
+  const int i = in ? base + lane : end - 1;
   {
-    M3 Fxz = field_from_leaves(clover_leaves(g, U, x, 0, 2));
-    for (int a = 0; a < 3; ++a)
-      for (int b = 0; b < 3; ++b) Fzx.a[a][b] = {-Fxz.a[a][b].r, -Fxz.a[a][b].i};
-  }
-  M3 Fxy = field_from_leaves(clover_leaves(g, U, x, 0, 1));
-  const double h = 0.5 * c_sw;
-  for (int blk = 0; blk < 2; ++blk) {
-    const double sg = blk == 0 ? 1.0 : -1.0;
-    cpx<double> E[3][3][3];  // E_l
-    for (int a = 0; a < 3; ++a)
-      for (int b = 0; b < 3; ++b) {
-        E[0][a][b] = sg * Fxt.a[a][b] - Fyz.a[a][b];
-        E[1][a][b] = sg * Fyt.a[a][b] - Fzx.a[a][b];
-        E[2][a][b] = sg * Fzt.a[a][b] - Fxy.a[a][b];
-      }
-    // M = (i h) [s1 (x) E0 + s2 (x) E1 + s3 (x) E2] + (4 + m0)
-    cpx<double> M[6][6];
-    for (int a = 0; a < 3; ++a)
-      for (int b = 0; b < 3; ++b) {
-        cpx<double> e0 = E[0][a][b], e1 = E[1][a][b], e2 = E[2][a][b];
-        // spin blocks of s1 e0 + s2 e1 + s3 e2: [[e2, e0 - i e1], [e0 + i e1, -e2]]
-        cpx<double> b00 = e2, b11 = {-e2.r, -e2.i};
-        cpx<double> b01 = e0 - times_i(e1), b10 = e0 + times_i(e1);
-        M[a][b] = h * times_i(b00);
-        M[a][3 + b] = h * times_i(b01);
-        M[3 + a][b] = h * times_i(b10);
-        M[3 + a][3 + b] = h * times_i(b11);
-      }
-    for (int k = 0; k < 6; ++k) M[k][k].r += 4.0 + m0;
-    if (p == 0) {
-      store_packed(cl_e, blk, i, vh, M);
-    } else {
-      if (cl_o) store_packed(cl_o, blk, i, vh, M);  // A_oo itself, for the full operator
-      if (!hpd_inverse6(M)) {
-        *notpd = 1;
-        for (int j = 0; j < 6; ++j)
-          for (int k = 0; k < 6; ++k) M[j][k] = {0.0, 0.0};
-      }
-      store_packed(cl_o_inv, blk, i, vh, M);
+    int mu, nu;
+    plane_dirs(w, mu, nu);
+    const AH3 F = field_strength(L, g, decode(g, i, p), p, mu, nu);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      Fs[w][k][lane] = F.d[k];
+      Fs[w][3 + 2 * k][lane] = F.u[k].r;
+      Fs[w][4 + 2 * k][lane] = F.u[k].i;
     }
+  }
+  __syncthreads();
+  if (w >= 2 || !in) return;
+  const int blk = w;
+  const double sg = blk == 0 ? 1.0 : -1.0, h = 0.5 * c_sw;
+  // E_l = sg F_lt - F_jk: planes (x,t), (y,t), (z,t) against (y,z), (z,x) = -(x,z), (x,y)
+  auto field = [&](int lt, int jk, double sjk) {
+    AH3 E;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      E.d[k] = sg * Fs[lt][k][lane] - sjk * Fs[jk][k][lane];
+      E.u[k] = {sg * Fs[lt][3 + 2 * k][lane] - sjk * Fs[jk][3 + 2 * k][lane],
+                sg * Fs[lt][4 + 2 * k][lane] - sjk * Fs[jk][4 + 2 * k][lane]};
+    }
+    return E;
+  };
+  const AH3 E0 = field(2, 3, 1.0), E1 = field(4, 1, -1.0), E2 = field(5, 0, 1.0);
+  // M = (i h) [s1 (x) E0 + s2 (x) E1 + s3 (x) E2] + (4 + m0), spin blocks of the bracket
+  // [[e2, e0 - i e1], [e0 + i e1, -e2]]: upper triangle
+  cpx<double> M[6][6];
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      const cpx<double> e0 = ah_at(E0, a, b), e1 = ah_at(E1, a, b), e2 = ah_at(E2, a, b);
+      if (a <= b) {
+        M[a][b] = h * times_i(e2);
+        M[3 + a][3 + b] = {-M[a][b].r, -M[a][b].i};
+      }
+      M[a][3 + b] = h * times_i(e0 - times_i(e1));
+    }
+#pragma unroll
+  for (int k = 0; k < 6; ++k) M[k][k].r += 4.0 + m0;
+  if (p == 0) {
+    store_packed<double>(out.e, blk, i, vh, M);
+    if (out.e32) store_packed<float>(out.e32, blk, i, vh, M);  // uniform
+  } else {
+    store_packed<double>(out.o, blk, i, vh, M);  // A_oo itself, for the full operator
+    if (!hpd_inverse6(M)) {
+      *notpd = 1;
+#pragma unroll
+      for (int j = 0; j < 6; ++j)
+#pragma unroll
+        for (int k = j; k < 6; ++k) M[j][k] = {0.0, 0.0};
+    }
+    store_packed<double>(out.o_inv, blk, i, vh, M);
+    if (out.o_inv32) store_packed<float>(out.o_inv32, blk, i, vh, M);
   }
 }
 
-hipError_t launch_clover_build(const Geo& g, const d2_t* U, double c_sw, double m0, d2_t* cl_e,
-                               d2_t* cl_o_inv, d2_t* cl_o, int* notpd, hipStream_t s) {
-  long long n = 2LL * g.Vh;
-  int blocks = (int)((n + 127) / 128);
-  hipLaunchKernelGGL(k_clover_build, dim3(blocks), dim3(128), 0, s, g, U, c_sw, m0, cl_e, cl_o_inv, cl_o,
-                     notpd);
+hipError_t launch_clover_build(const Geo& g, const d2_t* links_e, const d2_t* links_o, double c_sw, double m0,
+                               const ClovOut& out, int* notpd, hipStream_t s) {
+  const long long blocks = gauge_groups(g, 2);
+  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_clover_build, dim3((unsigned)blocks), dim3(64 * CLOVER_PLANES), 0, s, g,
+                     PackedLinks{{links_e, links_o}}, c_sw, m0, out, notpd);
   return hipGetLastError();
 }
 

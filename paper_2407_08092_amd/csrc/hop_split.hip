@@ -180,7 +180,7 @@ struct SplitArgs {
 };
 
 template <class P, int MODE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(typename P::R) == 8 ? 2 : 3)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(typename P::R) == 8 ? 1 : 3)))
 hop_split_kernel(SplitArgs a) {
   using R = typename P::R;
   __shared__ cpx<R> hs[8][6][64];
