@@ -288,7 +288,8 @@ hipError_t launch_any(ddq_lattice* L, const HopArgs<R>& a, int mode, bool dag, i
       return launch_hop_rb(b, mode, nrhs, L->stream);
     }
   }
-  if (!t && hop_split_takes(L->geo, sizeof(pair<R>), nrhs)) return launch_hop_split<R>(a, mode, dag, nrhs, L->stream);
+  if (mode == M_PREP || mode == M_RECON || (!t && hop_split_takes(L->geo, sizeof(pair<R>), nrhs)))
+    return launch_hop_split<R>(a, mode, dag, nrhs, L->stream);
   // one right-hand side per thread: the workgroup order of an nb = 0 tile set for
   // nrhs, else slab order
   b.tile = MrTile{};
@@ -624,27 +625,38 @@ int norm_host(ddq_lattice* L, const d2_t* v, long long n, double* out) {
   return DDQ_OK;
 }
 
-// eq. 2: b~_e = b_e - D_eo D_oo^-1 b_o = b_e + H_eo (A_oo^-1 b_o); bo: work vector(s)
-int prepare_impl(ddq_lattice* L, int nrhs, const d2_t* b, d2_t* bt_e, d2_t* bo) {
+// eq. 2: b~_e = b_e - D_eo D_oo^-1 b_o = b_e + H_eo (A_oo^-1 b_o), read from the full vector b;
+// into bt_e, or with b32 into FP32 vectors b32 = b~_e and x32 = omega b~_e
+int prepare_impl(ddq_lattice* L, int nrhs, const d2_t* b, d2_t* bt_e, f2_t* b32 = nullptr, f2_t* x32 = nullptr,
+                 float omega = 0.f) {
   CHK(ensure_tmp(L, DDQ_F64, nrhs));
   d2_t* u = (d2_t*)L->tmp[DDQ_F64].p;
-  HIPCHK(launch_pack_parity<double>(L->geo, 1, nrhs, b, bo, L->stream));
-  HIPCHK(launch_clover_only<double>(L->geo, nrhs, (const d2_t*)L->clov[DDQ_F64][1], bo, u, L->stream));
-  HIPCHK(launch_pack_parity<double>(L->geo, 0, nrhs, b, bt_e, L->stream));
-  HIPCHK(kernel_B<double>(L, DDQ_F64, nrhs, M_PREP, u, nullptr, bt_e, bt_e, 0.0, false));
+  HIPCHK(launch_clover_full(L->geo, 1, nrhs, (const d2_t*)L->clov[DDQ_F64][1], b, u, L->stream));
+  HopArgs<double> a = hop_args<double>(L, DDQ_F64, 0);
+  a.in = u;
+  a.b = b;
+  a.out = bt_e;
+  a.out32 = b32;
+  a.scaled32 = x32;
+  a.scale = omega;
+  HIPCHK(run_hop<double>(L, a, M_PREP, false, nrhs));
   return DDQ_OK;
 }
 
-// eq. 2: x_o = D_oo^-1 (b_o - D_oe x_e) = A_oo^-1 (b_o + H_oe x_e); bo, xo: work vectors
-int reconstruct_impl(ddq_lattice* L, int nrhs, const d2_t* x_e, const d2_t* b, d2_t* x, d2_t* bo, d2_t* xo) {
-  HIPCHK(launch_pack_parity<double>(L->geo, 1, nrhs, b, bo, L->stream));
+// eq. 2: x_o = D_oo^-1 (b_o - D_oe x_e) = A_oo^-1 (b_o + H_oe x_e), b_o read from and x_o written
+// to full vectors, and to xo unless null
+int reconstruct_odd(ddq_lattice* L, int nrhs, const d2_t* x_e, const d2_t* b, d2_t* x, d2_t* xo) {
   HopArgs<double> a = hop_args<double>(L, DDQ_F64, 1);
   a.in = x_e;
-  a.b = bo;
+  a.b = b;
+  a.full = x;
   a.out = xo;
   HIPCHK(run_hop<double>(L, a, M_RECON, false, nrhs));
+  return DDQ_OK;
+}
+int reconstruct_impl(ddq_lattice* L, int nrhs, const d2_t* x_e, const d2_t* b, d2_t* x, d2_t* xo = nullptr) {
+  CHK(reconstruct_odd(L, nrhs, x_e, b, x, xo));
   HIPCHK(launch_unpack_parity<double>(L->geo, 0, nrhs, x_e, x, L->stream));
-  HIPCHK(launch_unpack_parity<double>(L->geo, 1, nrhs, xo, x, L->stream));
   return DDQ_OK;
 }
 
@@ -1282,7 +1294,7 @@ int ddq_oe_prepare(ddq_lattice* L, int nrhs, const void* b, void* bt_e) {
   if (nrhs < 1 || !b || !bt_e) return fail(DDQ_ERR_ARG, "bad prepare arguments");
   if (b == bt_e) return fail(DDQ_ERR_ARG, "b and bt_e must not overlap");
   CHK(L->scratch64.ensure((size_t)nrhs * L->nvec() * 16));
-  return prepare_impl(L, nrhs, (const d2_t*)b, (d2_t*)bt_e, (d2_t*)L->scratch64.p);
+  return prepare_impl(L, nrhs, (const d2_t*)b, (d2_t*)bt_e);
 }
 
 int ddq_oe_reconstruct(ddq_lattice* L, int nrhs, const void* x_e, const void* b, void* x) {
@@ -1291,8 +1303,7 @@ int ddq_oe_reconstruct(ddq_lattice* L, int nrhs, const void* x_e, const void* b,
   if (x == b || x == x_e) return fail(DDQ_ERR_ARG, "x must not overlap b or x_e");
   const size_t nb = (size_t)nrhs * L->nvec();
   CHK(L->scratch64.ensure(2 * nb * 16));
-  d2_t* bo = (d2_t*)L->scratch64.p;
-  return reconstruct_impl(L, nrhs, (const d2_t*)x_e, (const d2_t*)b, (d2_t*)x, bo, bo + nb);
+  return reconstruct_impl(L, nrhs, (const d2_t*)x_e, (const d2_t*)b, (d2_t*)x);
 }
 
 int ddq_convert_parity(ddq_lattice* L, int nrhs, int src_prec, const void* src, int dst_prec, void* dst) {
@@ -1630,14 +1641,20 @@ int dirac_impl(ddq_lattice* L, int nrhs, const d2_t* x, d2_t* y, d2_t* ws) {
 
 // z = M_nu r for nrhs full FP64 vectors (Sect. 2.4.5): eq. 2 with D_S^-1 replaced by
 // p_{R,nu}(D_S) -- prepare, nu Richardson sweeps from zero in `prec`, reconstruct.
-// ws: 4 nrhs FP64 parity vectors; b32, x32: nrhs FP32 parity vectors (prec DDQ_F32).
+// ws: 2 nrhs FP64 parity vectors; b32, x32: nrhs FP32 parity vectors (prec DDQ_F32).
 int smoother_impl(ddq_lattice* L, int nrhs, const d2_t* r, d2_t* z, int nu, double omega, int prec, d2_t* ws,
                   f2_t* b32, f2_t* x32) {
   const size_t nb = (size_t)nrhs * L->nvec();
-  d2_t *bt = ws, *xe = ws + nb, *bo = ws + 2 * nb, *xo = ws + 3 * nb;
-  CHK(prepare_impl(L, nrhs, r, bt, bo));
+  d2_t *bt = ws, *xe = ws + nb;
+  if (prec == DDQ_F32 && nu > 0) {  // b~_e is needed in FP32 only; the first sweep from zero is omega b~_e
+    CHK(prepare_impl(L, nrhs, r, nullptr, b32, x32, (float)omega));
+    CHK(sweeps<float>(L, DDQ_F32, nrhs, x32, b32, nu - 1, (float)omega));
+    HIPCHK(launch_f32_to_parity_and_full(L->geo, 0, nrhs, x32, xe, z, L->stream));
+    return reconstruct_odd(L, nrhs, xe, r, z, nullptr);
+  }
+  CHK(prepare_impl(L, nrhs, r, bt));
   CHK(rich_prec_impl(L, nrhs, bt, xe, nu, omega, prec, b32, x32));
-  return reconstruct_impl(L, nrhs, xe, r, z, bo, xo);
+  return reconstruct_impl(L, nrhs, xe, r, z);
 }
 
 // the smoother's and the full operator's work vectors (8 FP64 + 2 FP32 parity vectors
@@ -1739,7 +1756,7 @@ int oe_solve_one(ddq_lattice* L, void* x, const void* b, const ddq_gmres_params*
   const double target = P->tol * bnorm;
 
   // eq. 2: b~_e, initial x_e from the even half of x
-  CHK(prepare_impl(L, 1, (const d2_t*)b, bt, w));
+  CHK(prepare_impl(L, 1, (const d2_t*)b, bt));
   HIPCHK(launch_pack_parity<double>(L->geo, 0, 1, (const d2_t*)x, xe, L->stream));
 
   KrylovOps ops;
@@ -1793,7 +1810,7 @@ int oe_solve_one(ddq_lattice* L, void* x, const void* b, const ddq_gmres_params*
     CHK(gmres_core(L, n, xe, V, Z, w, m, P->max_cycles - cycles, schur_target, red, passes, ops, run, status));
     cycles += run.cycles;
     iters += run.iters;
-    CHK(reconstruct_impl(L, 1, xe, (const d2_t*)b, (d2_t*)x, V, w));  // x_o in w
+    CHK(reconstruct_impl(L, 1, xe, (const d2_t*)b, (d2_t*)x, w));  // x_o in w
     CHK(full_residual_norm(L, xe, w, (const d2_t*)b, V, V + n, &full));
     if (!std::isfinite(full)) return fail(DDQ_ERR_NONFINITE, "full residual norm is not finite");
     if (full <= target) {
@@ -2442,7 +2459,7 @@ int ddq_batch_solve(ddq_batch* B, void* const* x, const void* const* b, const dd
     auto& S = B->sys[s];
     HIPCHK(launch_norm2_b((const d2_t*)b[s], 2 * S.n, S.nrhs, (double*)S.partial.p, S.nbx, S.hn, B->stream));
     CHK(fetch_norms(s));
-    CHK(prepare_impl(S.L, S.nrhs, (const d2_t*)b[s], S.bt, S.w));
+    CHK(prepare_impl(S.L, S.nrhs, (const d2_t*)b[s], S.bt));
     HIPCHK(launch_pack_parity<double>(S.L->geo, 0, S.nrhs, (const d2_t*)x[s], S.xe, B->stream));
   }
   HIPCHK(hipStreamSynchronize(B->stream));
@@ -2619,7 +2636,7 @@ int ddq_batch_solve(ddq_batch* B, void* const* x, const void* const* b, const dd
   // continue, so DDQ_OK always means the full bar
   for (auto& S : B->sys) {
     const int s = (int)(&S - B->sys.data());
-    CHK(reconstruct_impl(S.L, S.nrhs, S.xe, (const d2_t*)b[s], (d2_t*)x[s], S.w, S.z));
+    CHK(reconstruct_impl(S.L, S.nrhs, S.xe, (const d2_t*)b[s], (d2_t*)x[s], S.z));
   }
   bool retry = false;
   for (int s = 0; s < ns; ++s) {

@@ -14,11 +14,11 @@ namespace ddq {
 // then, with C the site's stored clover block (A_ee on even sites, A_oo^-1 on odd):
 enum HopMode {
   M_HOP_CLINV = 0,  // out = C h                      u_o = A_oo^-1 H_oe x_e   (kernel A)
-  M_RECON = 1,      // out = C (b + h)                x_o = A_oo^-1 (b_o + H_oe x_e)
+  M_RECON = 1,      // full = C (b + h)               x_o = A_oo^-1 (b_o + H_oe x_e), b and full full vectors
   M_APPLY = 2,      // out = C x - h                  y_e = A_ee x_e - H_eo u_o (kernel B)
   M_RICH = 3,       // out = x + w (b - C x + h)      Richardson sweep, in place
   M_RESID = 4,      // out = b - C x + h              r = b - D_S x
-  M_PREP = 5,       // out = b + h                    b~_e = b_e + H_eo u_o
+  M_PREP = 5,       // out = b + h                    b~_e = b_e + H_eo u_o, b a full vector
   M_NMODES = 6
 };
 
@@ -99,8 +99,13 @@ struct HopArgs {
   const pair<R>* links;      // 4 direction fields of LINK_ROWS complex rows, parity p_out
   const pair<R>* clov;       // clover field of CLOVER_ROWS complex rows, parity p_out
   const pair<R>* x;          // own-parity vector (APPLY, RICH, RESID)
-  const pair<R>* b;          // own-parity right-hand side (RECON, RICH, RESID, PREP)
+  const pair<R>* b;          // own-parity right-hand side (RICH, RESID); full vector (RECON, PREP)
   pair<R>* out;
+  // RECON: the full vector whose sites of parity p_out are written, besides out where that is not
+  // null.  PREP: unless null, out32 = the result in FP32 and scaled32 = scale out32 in place of out
+  pair<R>* full;
+  f2_t *out32, *scaled32;
+  float scale;
   R omega;
   int link12;                // FP32: links stored as their first two rows
   int nblk;                  // workgroups along x, padded to a multiple of 8 (one right-hand side)
@@ -138,7 +143,7 @@ hipError_t launch_hop(const HopArgs<R>& a, int mode, bool dagger, int nrhs, hipS
 template <typename R>
 hipError_t launch_hop_stream(const HopArgs<R>& a, int mode, hipStream_t s);
 
-// the same launches (any mode; no tile) on four threads per site, bit for bit the results of
+// the same launches (no tile; M_PREP and M_RECON only here) on four threads per site, bit for bit the results of
 // launch_hop and launch_hop16: for launches of few sites (hop_split.hip)
 bool hop_split_takes(const Geo& g, int bytes_per_complex, int nrhs);
 template <typename R>
@@ -213,10 +218,9 @@ hipError_t launch_h16_to_f32(int kind, void* y, const void* x, float scale, int 
 hipError_t launch_links_to_h16(int kind, const d2_t* in, void* out, int vh, hipStream_t s);
 hipError_t launch_clover_to_h16(int kind, const d2_t* in, void* out, int vh, hipStream_t s);
 
-// out = C v for every site of one parity (C = that parity's stored clover blocks)
-template <typename R>
-hipError_t launch_clover_only(const Geo& g, int nrhs, const pair<R>* clov, const pair<R>* v, pair<R>* out,
-                              hipStream_t s);
+// out = C v on the sites of one parity (C = that parity's stored clover blocks): full a full FP64
+// vector, out a parity vector
+hipError_t launch_clover_full(const Geo& g, int parity, int nrhs, const d2_t* clov, const d2_t* full, d2_t* out, hipStream_t s);
 
 // FP64 vector kernels (complex128 vectors of n elements)
 hipError_t launch_dot_partial(const d2_t* V, long long vstride, int k, const d2_t* w, long long n,
@@ -298,5 +302,9 @@ hipError_t launch_pack_parity(const Geo& g, int parity, int nrhs, const pair<R>*
 template <typename R>
 hipError_t launch_unpack_parity(const Geo& g, int parity, int nrhs, const pair<R>* v, pair<R>* full,
                                 hipStream_t s);
+
+// FP32 parity vectors -> FP64 parity vectors v and the sites of `parity` of full FP64 vectors
+hipError_t launch_f32_to_parity_and_full(const Geo& g, int parity, int nrhs, const void* src, d2_t* v, d2_t* full,
+                                         hipStream_t s);
 
 }  // namespace ddq

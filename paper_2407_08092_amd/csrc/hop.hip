@@ -7,6 +7,7 @@
 // eight incident links (forward U_mu(x) and pre-daggered backward U_mu(x-mu)^H),
 // so link reads never gather.  Kernel A (odd output) and kernel B (even output)
 // are one template with different epilogues (HopMode).
+#include "full_rows.h"
 #include "hop_common.h"
 
 namespace ddq {
@@ -122,13 +123,6 @@ hop_kernel(HopArgs<R> a) {
   const Field out = vfield(a.out + roff, SP_E, vh);  // may alias a.x (in-place Richardson)
   if constexpr (MODE == M_HOP_CLINV) {
     store_spinor<R, ST>(out, off, clover_mul<R, CLV>(cl, coff, acc));
-  } else if constexpr (MODE == M_RECON) {
-    Spinor<R> bb = load_spinor<R, OWN>(vfield(a.b + roff, SP_E, vh), off);
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-      for (int cc = 0; cc < 3; ++cc) bb.c[sp][cc] = bb.c[sp][cc] + acc.c[sp][cc];
-    store_spinor<R, ST>(out, off, clover_mul<R, CLV>(cl, coff, bb));
   } else if constexpr (MODE == M_APPLY) {
     Spinor<R> cx = clover_mul<R, CLV>(cl, coff, load_spinor<R, OWN>(vfield(a.x + roff, SP_E, vh), off));
 #pragma unroll
@@ -148,20 +142,13 @@ hop_kernel(HopArgs<R> a) {
         xx.c[sp][cc] = xx.c[sp][cc] + a.omega * r;
       }
     store_spinor<R, ST>(out, off, xx);
-  } else if constexpr (MODE == M_RESID) {
+  } else {  // M_RESID
     Spinor<R> bb = load_spinor<R, OWN>(vfield(a.b + roff, SP_E, vh), off);
     Spinor<R> cx = clover_mul<R, CLV>(cl, coff, load_spinor<R, OWN>(vfield(a.x + roff, SP_E, vh), off));
 #pragma unroll
     for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
       for (int cc = 0; cc < 3; ++cc) bb.c[sp][cc] = bb.c[sp][cc] - cx.c[sp][cc] + acc.c[sp][cc];
-    store_spinor<R, ST>(out, off, bb);
-  } else {  // M_PREP
-    Spinor<R> bb = load_spinor<R, OWN>(vfield(a.b + roff, SP_E, vh), off);
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-      for (int cc = 0; cc < 3; ++cc) bb.c[sp][cc] = bb.c[sp][cc] + acc.c[sp][cc];
     store_spinor<R, ST>(out, off, bb);
   }
 }
@@ -317,39 +304,35 @@ hipError_t launch_hop(const HopArgs<R>& a0, int mode, bool dagger, int nrhs, hip
     case M_APPLY: return launch_mode<R, M_APPLY>(a, dagger, nrhs, s);
     case M_RICH: return launch_mode<R, M_RICH>(a, dagger, nrhs, s);
   }
-  if constexpr (sizeof(R) == 8) {  // eq. 2 and the residual run in FP64
-    switch (mode) {
-      case M_RECON: return launch_mode<R, M_RECON>(a, dagger, nrhs, s);
-      case M_RESID: return launch_mode<R, M_RESID>(a, dagger, nrhs, s);
-      case M_PREP: return launch_mode<R, M_PREP>(a, dagger, nrhs, s);
-    }
-  }
+  if constexpr (sizeof(R) == 8)  // the residual runs in FP64
+    if (mode == M_RESID) return launch_mode<R, M_RESID>(a, dagger, nrhs, s);
   return hipErrorInvalidValue;
 }
 
-template <typename R>
-__global__ void __launch_bounds__(HOP_BLOCK) k_clover_only(Geo g, const pair<R>* __restrict__ clov,
-                                                            const pair<R>* __restrict__ v, pair<R>* __restrict__ out) {
-  const int vh = g.Vh;
-  const int i = blockIdx.x * HOP_BLOCK + (int)threadIdx.x;
+// out = C v on the sites of one parity, v a full FP64 vector, out a parity vector
+__global__ void __launch_bounds__(HOP_BLOCK) k_clover_full(Geo g, int parity, const d2_t* __restrict__ clov,
+                                                           const u4a8_t* __restrict__ full, d2_t* __restrict__ out) {
+  __shared__ u4_t lds[HOP_BLOCK / 64][SPINOR_ROWS][FULL_ROW];
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+  const int base = ((int)blockIdx.x * (HOP_BLOCK / 64) + w) * 64, vh = g.Vh;
+  if (base >= vh) return;  // uniform over a wavefront
+  const size_t r = (size_t)blockIdx.y * SPINOR_ROWS * (size_t)vh;
+  FullRows<SPINOR_ROWS>(g, base, min(base + 64, vh), parity, lane).load<64>(full + 2 * r, lds[w], lane);
+  wave_lds_order();
+  const int i = base + lane;
   if (i >= vh) return;
-  const size_t roff = (size_t)blockIdx.y * 12 * (size_t)vh;
-  constexpr int SP_E = SPINOR_ROWS / CPE<R>;
-  store_spinor<R>(vfield(out + roff, SP_E, vh), voff(i),
-                  clover_mul<R>(bfield(clov, CLOVER_ROWS / CPE<R>, vh), boff(i, CLOVER_ROWS / CPE<R>),
-                                load_spinor<R>(vfield(v + roff, SP_E, vh), voff(i))));
+  Spinor<double> v;
+#pragma unroll
+  for (int k = 0; k < SPINOR_ROWS; ++k) unpack<double>(lds[w][k][lane], &v.c[k / 3][k % 3]);
+  store_spinor<double>(vfield(out + r, SPINOR_ROWS, vh), voff(i),
+                       clover_mul<double>(bfield(clov, CLOVER_ROWS, vh), boff(i, CLOVER_ROWS), v));
 }
 
-template <typename R>
-hipError_t launch_clover_only(const Geo& g, int nrhs, const pair<R>* clov, const pair<R>* v, pair<R>* out,
-                              hipStream_t s) {
-  dim3 grid((g.Vh + HOP_BLOCK - 1) / HOP_BLOCK, nrhs);
-  hipLaunchKernelGGL((k_clover_only<R>), grid, dim3(HOP_BLOCK), 0, s, g, clov, v, out);
+hipError_t launch_clover_full(const Geo& g, int parity, int nrhs, const d2_t* clov, const d2_t* full, d2_t* out, hipStream_t s) {
+  const dim3 grid((g.Vh + HOP_BLOCK - 1) / HOP_BLOCK, nrhs);
+  hipLaunchKernelGGL(k_clover_full, grid, dim3(HOP_BLOCK), 0, s, g, parity, clov, (const u4a8_t*)full, out);
   return hipGetLastError();
 }
-
-template hipError_t launch_clover_only<double>(const Geo&, int, const d2_t*, const d2_t*, d2_t*, hipStream_t);
-template hipError_t launch_clover_only<float>(const Geo&, int, const f2_t*, const f2_t*, f2_t*, hipStream_t);
 
 template hipError_t launch_hop<double>(const HopArgs<double>&, int, bool, int, hipStream_t);
 template hipError_t launch_hop<float>(const HopArgs<float>&, int, bool, int, hipStream_t);

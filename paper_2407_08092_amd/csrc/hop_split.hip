@@ -15,6 +15,7 @@
 // What bounds it: the launch itself (about 4 us from one launch to the next) up to 10^4 sites,
 // then the caches' bandwidth; 4^4 FP64 8.4 -> 5.3 us a launch, 16^4 FP32 12.6 -> 8.3, 24^3 x 48
 // FP32 71 -> 62 (6.2 TB/s of its algorithmic bytes).
+#include "full_rows.h"
 #include "hop_common.h"
 #include "hop_h16.h"
 
@@ -177,6 +178,10 @@ struct SplitArgs {
   int dagger;
   int slab;         // slab order; else the groups of 64 sites in a row
   int t_lo, t_cnt;  // output sites of slices [t_lo, t_lo + t_cnt)
+  // M_PREP, M_RECON: b is a full FP64 vector
+  void* full;       // M_RECON: the full vector whose sites of parity p_out are written (and, unless null, out)
+  void *out32, *scaled32;  // M_PREP: unless null, the result in FP32 and scale times that, in place of out
+  float scale;
 };
 
 template <class P, int MODE>
@@ -185,6 +190,8 @@ hop_split_kernel(SplitArgs a) {
   using R = typename P::R;
   __shared__ cpx<R> hs[8][6][64];
   __shared__ cpx<R> ex[MODE == M_HOP_CLINV || MODE == M_RECON ? 12 : 1][64];
+  constexpr bool FULL = MODE == M_RECON || MODE == M_PREP;
+  __shared__ u4_t rows[FULL ? SPINOR_ROWS : 1][FULL_ROW];
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
   int base, end, rhs;
   if (a.slab) {  // uniform
@@ -206,6 +213,9 @@ hop_split_kernel(SplitArgs a) {
   const Nbr nb = neighbours(a.g, decode(a.g, i, a.p_out));
   const R sf = a.dagger ? R(1) : R(-1), sb = -sf;  // D: forward (1 - g), backward (1 + g)
   const uint32_t off = voff(i);
+  const size_t fb = (size_t)rhs * 2 * SPINOR_ROWS * (size_t)vh;  // FULL: this right-hand side's full vectors
+  const FullRows<SPINOR_ROWS> fr(a.g, base, end, a.p_out, lane);
+  if constexpr (FULL) fr.template load<256>((const u4a8_t*)a.b + fb, rows, (int)threadIdx.x);
 
   const Field in = vec(a.in);
   const int jf = w == 0 ? nb.j[0] : w == 1 ? nb.j[2] : w == 2 ? nb.j[4] : nb.j[6];
@@ -235,7 +245,7 @@ hop_split_kernel(SplitArgs a) {
       hs[2 * w + 1][k][lane] = hb.c[k / 3][k % 3];
     }
   }
-  if constexpr (MODE == M_RICH || MODE == M_RESID || MODE == M_RECON || MODE == M_PREP) {
+  if constexpr (MODE == M_RICH || MODE == M_RESID) {
     const Field bv = vec(a.b);
 #pragma unroll
     for (int c = 0; c < 3; ++c) bs[c] = P::row(bv, 3 * w + c, off);
@@ -256,6 +266,9 @@ hop_split_kernel(SplitArgs a) {
   }
 #pragma unroll
   for (int c = 0; c < 3; ++c) h[c] = R(0.5) * h[c];
+  if constexpr (FULL)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) unpack<R>(rows[3 * w + c][lane], bs + c);
   cpx<R> o[3];
   if constexpr (MODE == M_PREP) {
 #pragma unroll
@@ -287,13 +300,35 @@ hop_split_kernel(SplitArgs a) {
       if constexpr (MODE == M_RICH) o[c] = xo + (R)a.omega * (bs[c] - o[c] + h[c]);
     }
   }
-  if (ok) {
-    const Field out = vec(a.out);
+  if constexpr (MODE == M_RECON) {
+    // every row of b is read (the barrier above): the results take their place
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      P::put(out, 3 * w + c, off, o[c]);
-      store_fence();
+    for (int c = 0; c < 3; ++c) rows[3 * w + c][lane] = pack<R>(o + c);
+    __syncthreads();
+    fr.template store<256>((u4a8_t*)a.full + fb, rows, (int)threadIdx.x);
+    if (!a.out) return;  // uniform
+  }
+  if (!ok) return;
+  if constexpr (MODE == M_PREP) {
+    if (a.out32) {  // uniform
+      using F = SplitR<float, false, true>;
+      const size_t r32 = (size_t)rhs * F::SP_E * (size_t)vh * 16;
+      const Field y = vfield((char*)a.out32 + r32, F::SP_E, vh), z = vfield((char*)a.scaled32 + r32, F::SP_E, vh);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const cpx<float> v = {(float)o[c].r, (float)o[c].i};
+        F::put(y, 3 * w + c, off, v);
+        F::put(z, 3 * w + c, off, {v.r * a.scale, v.i * a.scale});
+        store_fence();
+      }
+      return;
     }
+  }
+  const Field out = vec(a.out);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    P::put(out, 3 * w + c, off, o[c]);
+    store_fence();
   }
 }
 
@@ -350,7 +385,24 @@ static hipError_t split_launch_r(const SplitArgs& a, int mode, hipStream_t s) {
 
 template <typename R>
 hipError_t launch_hop_split(const HopArgs<R>& h, int mode, bool dagger, int nrhs, hipStream_t s) {
-  SplitArgs a{h.g, h.p_out, h.in, h.links, h.clov, h.x, h.b, h.out, (double)h.omega, nrhs, dagger ? 1 : 0, 0, h.t_lo, h.t_cnt};
+  SplitArgs a{};
+  a.g = h.g;
+  a.p_out = h.p_out;
+  a.in = h.in;
+  a.links = h.links;
+  a.clov = h.clov;
+  a.x = h.x;
+  a.b = h.b;
+  a.out = h.out;
+  a.omega = (double)h.omega;
+  a.nrhs = nrhs;
+  a.dagger = dagger ? 1 : 0;
+  a.t_lo = h.t_lo;
+  a.t_cnt = h.t_cnt;
+  a.full = h.full;
+  a.out32 = h.out32;
+  a.scaled32 = h.scaled32;
+  a.scale = h.scale;
   if (nrhs < 1 || a.t_lo < 0 || a.t_cnt < 0 || a.t_lo + a.t_cnt > a.g.L[3]) return hipErrorInvalidValue;
   if constexpr (sizeof(R) == 4)
     if (h.link12) return split_launch_r<float, true>(a, mode, s);
@@ -360,7 +412,17 @@ template hipError_t launch_hop_split<double>(const HopArgs<double>&, int, bool, 
 template hipError_t launch_hop_split<float>(const HopArgs<float>&, int, bool, int, hipStream_t);
 
 hipError_t launch_hop16_split(int kind, const Hop16Args& h, int mode, hipStream_t s) {
-  const SplitArgs a{h.g, h.p_out, h.in, h.links, h.clov32 ? (const void*)h.clov32 : h.clov, h.x, h.b, h.out, (double)h.omega, h.nrhs, 0, 0, 0, 0};
+  SplitArgs a{};
+  a.g = h.g;
+  a.p_out = h.p_out;
+  a.in = h.in;
+  a.links = h.links;
+  a.clov = h.clov32 ? (const void*)h.clov32 : h.clov;
+  a.x = h.x;
+  a.b = h.b;
+  a.out = h.out;
+  a.omega = (double)h.omega;
+  a.nrhs = h.nrhs;
   if (h.nrhs < 1) return hipErrorInvalidValue;
   if (kind == H16_BF16)
     return h.clov32 ? split_launch<Split16<__bf16, true>>(a, mode, s) : split_launch<Split16<__bf16, false>>(a, mode, s);
