@@ -603,10 +603,10 @@ int reserve_impl(ddq_lattice* L) {
   return DDQ_OK;
 }
 
-// |v|^2 of n complex128 elements into device scalar dst
-int norm2_dev(ddq_lattice* L, const d2_t* v, long long n, double* dst) {
+// |v|^2 of n complex128 elements into device scalar dst and, unless null, a pinned host one
+int norm2_dev(ddq_lattice* L, const d2_t* v, long long n, double* dst, double* host = nullptr) {
   HIPCHK(launch_norm2_partial(v, n, (double*)L->partial.p, L->nbx, L->stream));
-  HIPCHK(launch_reduce_real((const double*)L->partial.p, L->nbx, dst, L->stream));
+  HIPCHK(launch_reduce_real((const double*)L->partial.p, L->nbx, dst, host, L->stream));
   return DDQ_OK;
 }
 
@@ -618,9 +618,9 @@ int fetch(ddq_lattice* L, const void* dev, size_t bytes) {
 }
 
 int norm_host(ddq_lattice* L, const d2_t* v, long long n, double* out) {
-  double* d = (double*)L->small.p;
-  CHK(norm2_dev(L, v, n, d));
-  CHK(fetch(L, d, sizeof(double)));
+  CHK(ensure_host(L, sizeof(double)));
+  CHK(norm2_dev(L, v, n, (double*)L->small.p, L->host));
+  HIPCHK(hipStreamSynchronize(L->stream));
   *out = std::sqrt(L->host[0]);
   return DDQ_OK;
 }
@@ -1500,7 +1500,10 @@ Givens make_givens(cd a, cd b) {
 // Gram-Schmidt in `passes` passes, Givens rotations on the host, a cycle ends at
 // max(target, red * beta) or on breakdown; convergence only on the recomputed
 // residual at a restart.  x is updated in place; V holds m + 1 vectors, Z m, w one.
+// scale(w, a, v), where given, forms v = a w together with what precop(v, ..) starts from (the
+// next call is precop on that v).
 struct KrylovOps {
+  std::function<int(const d2_t*, double, d2_t*)> scale;
   std::function<int(const d2_t*, d2_t*)> resid;
   std::function<int(const d2_t*, d2_t*, d2_t*)> precop;
 };
@@ -1518,6 +1521,11 @@ int gmres_core(ddq_lattice* L, long long n, d2_t* x, d2_t* V, d2_t* Z, d2_t* w, 
   std::vector<cd> Hcol(m + 2), g(m + 2), y(m + 1);
   std::vector<std::vector<cd>> R(m, std::vector<cd>(m + 1));
   std::vector<Givens> rot(m);
+  auto scale = [&](const d2_t* in, double a, d2_t* out) -> int {
+    if (ops.scale) return ops.scale(in, a, out);
+    HIPCHK(launch_scale(out, in, a, n, L->stream));
+    return DDQ_OK;
+  };
   status = DDQ_NOT_CONVERGED;
   double beta = 0.0;
   int cycles, iters = 0;
@@ -1531,7 +1539,7 @@ int gmres_core(ddq_lattice* L, long long n, d2_t* x, d2_t* V, d2_t* Z, d2_t* w, 
       break;
     }
     if (cycles == max_cycles) break;
-    HIPCHK(launch_scale(V, V, 1.0 / beta, n, L->stream));
+    CHK(scale(V, 1.0 / beta, V));
     std::fill(g.begin(), g.end(), cd(0.0));
     g[0] = beta;
     const double cycle_target = std::max(target, red * beta);
@@ -1545,11 +1553,14 @@ int gmres_core(ddq_lattice* L, long long n, d2_t* x, d2_t* V, d2_t* Z, d2_t* w, 
       for (int pass = 0; pass < passes; ++pass) {
         d2_t* h = hdev + pass * 128;
         HIPCHK(launch_dot_partial(V, n, kk, w, n, (d2_t*)L->partial.p, L->nbx, L->stream));
-        HIPCHK(launch_reduce_partial((const d2_t*)L->partial.p, L->nbx, kk, h, L->stream));
-        HIPCHK(launch_update(w, V, n, kk, h, -1.0, n, L->stream));
+        // the coefficients and the norm also go straight to the pinned host buffer
+        HIPCHK(launch_reduce_partial((const d2_t*)L->partial.p, L->nbx, kk, h, (d2_t*)L->host + pass * 128, L->stream));
+        if (pass + 1 < passes)
+          HIPCHK(launch_update(w, V, n, kk, h, -1.0, n, L->stream));
+        else
+          HIPCHK(launch_update_norm(w, V, n, kk, h, -1.0, n, (double*)L->partial.p, L->nbx, ndev, L->host + 512, L->stream));
       }
-      CHK(norm2_dev(L, w, n, ndev));
-      CHK(fetch(L, hdev, 256 * sizeof(d2_t) + sizeof(double)));
+      HIPCHK(hipStreamSynchronize(L->stream));
       const double* hh = L->host;
       for (int j = 0; j < kk; ++j)
         Hcol[j] = passes == 2 ? cd(hh[2 * j] + hh[256 + 2 * j], hh[2 * j + 1] + hh[256 + 2 * j + 1])
@@ -1573,7 +1584,7 @@ int gmres_core(ddq_lattice* L, long long n, d2_t* x, d2_t* V, d2_t* Z, d2_t* w, 
       k_used = kk;
       const double est = std::abs(g[kk]);
       if (est <= cycle_target || hn <= 1e-14 * beta) break;
-      HIPCHK(launch_scale(V + (size_t)kk * n, w, 1.0 / hn, n, L->stream));
+      CHK(scale(w, 1.0 / hn, V + (size_t)kk * n));
     }
     // y = R^-1 g, x += Z y (or V y)
     for (int j = k_used - 1; j >= 0; --j) {
@@ -1693,9 +1704,10 @@ int full_residual_norm(ddq_lattice* L, const d2_t* xe, const d2_t* xo, const d2_
   a.out = t_o;
   HIPCHK(run_hop<double>(L, a, M_RESID, false, 1));
   double* d = (double*)L->small.p;
-  CHK(norm2_dev(L, t_e, n, d));
-  CHK(norm2_dev(L, t_o, n, d + 1));
-  CHK(fetch(L, d, 2 * sizeof(double)));
+  CHK(ensure_host(L, 2 * sizeof(double)));
+  CHK(norm2_dev(L, t_e, n, d, L->host));
+  CHK(norm2_dev(L, t_o, n, d + 1, L->host + 1));
+  HIPCHK(hipStreamSynchronize(L->stream));
   *out = std::sqrt(L->host[0] + L->host[1]);
   return DDQ_OK;
 }
@@ -1764,28 +1776,36 @@ int oe_solve_one(ddq_lattice* L, void* x, const void* b, const ddq_gmres_params*
     ++applies64;
     return resid<double>(L, DDQ_F64, 1, xx, bt, r);
   };
+  // v = a w and, in the preconditioner's precision, b = v and x = omega b, the first sweep from
+  // zero.  16-bit storage: v (unit norm) scaled by sqrt(n) so its entries are of order one, b16 =
+  // s v, x16 = omega s v, later back with 1/s (the sweeps are linear in b: the scale cancels exactly)
+  const double sc = std::sqrt((double)n);
+  void* b16 = b32;
+  void* x16 = (char*)b32 + (size_t)n * 4;
+  if (lo)
+    ops.scale = [&](const d2_t* in, double a, d2_t* v) -> int {
+      if (s16)
+        HIPCHK(launch_scale_to_h16(h16_kind(sp), v, in, a, b16, sc, x16, sc * P->omega, (int)L->Vh, L->stream));
+      else if (nu > 0)
+        HIPCHK(launch_scale_to_f32(v, in, a, b32, x32, (float)P->omega, (int)L->Vh, L->stream));
+      else
+        HIPCHK(launch_scale_to_f32(v, in, a, x32, nullptr, 0.f, (int)L->Vh, L->stream));
+      return DDQ_OK;
+    };
   // z_k = M v_k, w = D_S z_k
   ops.precop = [&](const d2_t* vk, d2_t* zk, d2_t* ww) -> int {
     if (lo) {
       if (s16) {
-        // the same sweeps on 16-bit storage: v_k (unit norm) scaled by sqrt(n) so its
-        // entries are of order one, b16 = s v, x16 = omega s v, then back with 1/s
-        // (the sweeps are linear in b, so the scale cancels exactly)
-        const double sc = std::sqrt((double)n);
-        void* b16 = b32;
-        void* x16 = (char*)b32 + (size_t)n * 4;
-        HIPCHK(launch_parity_to_h16(h16_kind(sp), b16, vk, sc, 1, (int)L->Vh, L->stream));
-        HIPCHK(launch_parity_to_h16(h16_kind(sp), x16, vk, sc * P->omega, 1, (int)L->Vh, L->stream));
         CHK(sweeps16(L, sp, 1, x16, b16, nu - 1, (float)P->omega));
-        HIPCHK(launch_h16_to_f32(h16_kind(sp), x32, x16, (float)(1.0 / sc), 1, (int)L->Vh, L->stream));
-        applies_lo += nu - 1;
-      } else if (nu > 0) {
-        CHK(rich_prec_impl(L, 1, vk, zk, nu, P->omega, DDQ_F32, b32, x32));
+        HIPCHK(launch_h16_to_f32(h16_kind(sp), x32, x16, (float)(1.0 / sc), 1, (int)L->Vh, L->stream, zk));
         applies_lo += nu - 1;
       } else {
-        HIPCHK(launch_parity_to_f32(x32, vk, 1, (int)L->Vh, L->stream));
+        if (nu > 0) {
+          CHK(sweeps<float>(L, DDQ_F32, 1, x32, b32, nu - 1, (float)P->omega));
+          applies_lo += nu - 1;
+        }
+        HIPCHK(launch_parity_to_f64(zk, x32, 1, (int)L->Vh, L->stream));
       }
-      if (s16 || nu == 0) HIPCHK(launch_parity_to_f64(zk, x32, 1, (int)L->Vh, L->stream));
       CHK(schur<float>(L, DDQ_F32, 1, x32, w32, false));
       ++applies_lo;
       HIPCHK(launch_parity_to_f64(ww, w32, 1, (int)L->Vh, L->stream));

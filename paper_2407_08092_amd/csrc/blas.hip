@@ -86,9 +86,10 @@ hipError_t launch_dot_partial(const d2_t* V, long long vstride, int k, const d2_
   return hipGetLastError();
 }
 
-// out[j] = sum_b partial[j * nbx + b], one workgroup per j
+// out[j] = sum_b partial[j * nbx + b], one workgroup per j; also into the pinned host array
+// `host` unless null, which the caller reads after a synchronisation, without a copy
 __global__ void __launch_bounds__(RB) k_reduce_partial(const d2_t* __restrict__ partial, int nbx,
-                                                       d2_t* __restrict__ out) {
+                                                       d2_t* __restrict__ out, d2_t* __restrict__ host) {
   __shared__ double lds[4 * 2];
   const int j = blockIdx.x;
   double v[2] = {0.0, 0.0};
@@ -103,22 +104,26 @@ __global__ void __launch_bounds__(RB) k_reduce_partial(const d2_t* __restrict__ 
     o.x = v[0];
     o.y = v[1];
     out[j] = o;
+    if (host) host[j] = o;
   }
 }
 
-hipError_t launch_reduce_partial(const d2_t* partial, int nbx, int k, d2_t* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce_partial, dim3(k), dim3(RB), 0, s, partial, nbx, out);
+hipError_t launch_reduce_partial(const d2_t* partial, int nbx, int k, d2_t* out, d2_t* host, hipStream_t s) {
+  hipLaunchKernelGGL(k_reduce_partial, dim3(k), dim3(RB), 0, s, partial, nbx, out, host);
   return hipGetLastError();
 }
 
-// w[e] += sign * sum_j V_j[e] h[j]
+// w[e] += sign * sum_j V_j[e] h[j]; NORM: partial[bx] = the workgroup's part of |w|^2 after it
+template <bool NORM>
 __global__ void __launch_bounds__(RB) k_update(d2_t* __restrict__ w, const d2_t* __restrict__ V,
                                                long long vstride, int k, const d2_t* __restrict__ h,
-                                               double sign, long long n) {
+                                               double sign, long long n, double* __restrict__ partial) {
   __shared__ d2_t hs[256];
+  __shared__ double lds[4];
   for (int j = threadIdx.x; j < k; j += RB) hs[j] = h[j];
   __syncthreads();
   const long long stride = (long long)gridDim.x * RB;
+  double norm[1] = {0.0};
   for (long long e = (long long)blockIdx.x * RB + threadIdx.x; e < n; e += stride) {
     double ar = 0.0, ai = 0.0;
     for (int j = 0; j < k; ++j) {
@@ -132,6 +137,11 @@ __global__ void __launch_bounds__(RB) k_update(d2_t* __restrict__ w, const d2_t*
     we.y = fma(sign, ai, we.y);
     w[e] = we;
     store_fence();
+    if constexpr (NORM) norm[0] = fma(we.x, we.x, fma(we.y, we.y, norm[0]));
+  }
+  if constexpr (NORM) {
+    block_sum<1>(norm, lds);
+    if (threadIdx.x == 0) partial[blockIdx.x] = norm[0];
   }
 }
 
@@ -143,8 +153,19 @@ static int grid_for(long long n) {
 hipError_t launch_update(d2_t* w, const d2_t* V, long long vstride, int k, const d2_t* h, double sign,
                          long long n, hipStream_t s) {
   if (k > 256) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_update, dim3(grid_for(n)), dim3(RB), 0, s, w, V, vstride, k, h, sign, n);
+  hipLaunchKernelGGL(k_update<false>, dim3(grid_for(n)), dim3(RB), 0, s, w, V, vstride, k, h, sign, n, (double*)nullptr);
   return hipGetLastError();
+}
+
+// the update and |w|^2 after it, into the device scalar norm2 and the pinned host one
+hipError_t launch_update_norm(d2_t* w, const d2_t* V, long long vstride, int k, const d2_t* h, double sign, long long n,
+                              double* partial, int nbx, double* norm2, double* host, hipStream_t s) {
+  if (k > 256) return hipErrorInvalidValue;
+  const int grid = min(grid_for(n), nbx);
+  hipLaunchKernelGGL(k_update<true>, dim3(grid), dim3(RB), 0, s, w, V, vstride, k, h, sign, n, partial);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return launch_reduce_real(partial, grid, norm2, host, s);
 }
 
 __global__ void __launch_bounds__(RB) k_norm2_partial(const d2_t* __restrict__ w, long long n,
@@ -166,16 +187,19 @@ hipError_t launch_norm2_partial(const d2_t* w, long long n, double* partial, int
 }
 
 __global__ void __launch_bounds__(RB) k_reduce_real(const double* __restrict__ partial, int nbx,
-                                                    double* __restrict__ out) {
+                                                    double* __restrict__ out, double* __restrict__ host) {
   __shared__ double lds[4];
   double v[1] = {0.0};
   for (int b = threadIdx.x; b < nbx; b += RB) v[0] += partial[b];
   block_sum<1>(v, lds);
-  if (threadIdx.x == 0) *out = v[0];
+  if (threadIdx.x == 0) {
+    *out = v[0];
+    if (host) *host = v[0];
+  }
 }
 
-hipError_t launch_reduce_real(const double* partial, int nbx, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce_real, dim3(1), dim3(RB), 0, s, partial, nbx, out);
+hipError_t launch_reduce_real(const double* partial, int nbx, double* out, double* host, hipStream_t s) {
+  hipLaunchKernelGGL(k_reduce_real, dim3(1), dim3(RB), 0, s, partial, nbx, out, host);
   return hipGetLastError();
 }
 
@@ -248,6 +272,29 @@ __global__ void k_scale_f32(f2_t* __restrict__ y, const f2_t* __restrict__ x, fl
 
 hipError_t launch_scale_f32(f2_t* y, const f2_t* x, float a, long long n, hipStream_t s) {
   hipLaunchKernelGGL(k_scale_f32, dim3(grid_for(n)), dim3(RB), 0, s, y, x, a, n);
+  return hipGetLastError();
+}
+
+// v = a w (FP64 parity vectors; v may be w) and its FP32 form b32, x32 = omega b32 (x32 may be
+// null): a new Krylov vector with what its preconditioner starts from, w read once
+__global__ void __launch_bounds__(RB) k_scale_to_f32(d2_t* v, const d2_t* w, double a, f4_t* __restrict__ b32,
+                                                     f4_t* __restrict__ x32, float omega, int vh) {
+  const int t = (int)(blockIdx.x * RB + threadIdx.x);  // (row pair k, site)
+  if (t >= 6 * vh) return;
+  const int k = t / vh, i = t - k * vh;
+  const size_t e0 = (size_t)(2 * k) * vh + i, e1 = e0 + vh;
+  const d2_t p = w[e0] * a, q = w[e1] * a;
+  v[e0] = p;
+  v[e1] = q;
+  const f4_t o = {(float)p.x, (float)p.y, (float)q.x, (float)q.y};
+  b32[t] = o;
+  if (x32) x32[t] = o * omega;
+}
+
+hipError_t launch_scale_to_f32(d2_t* v, const d2_t* w, double a, void* b32, void* x32, float omega, int vh, hipStream_t s) {
+  const long long n = 6LL * vh;
+  if (n > 0x7fffffffLL - RB) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_scale_to_f32, dim3((unsigned)((n + RB - 1) / RB)), dim3(RB), 0, s, v, w, a, (f4_t*)b32, (f4_t*)x32, omega, vh);
   return hipGetLastError();
 }
 

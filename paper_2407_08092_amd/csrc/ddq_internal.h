@@ -214,7 +214,10 @@ hipError_t launch_hop16(int kind, const Hop16Args& a, int mode, hipStream_t s);
 hipError_t launch_hop16_split(int kind, const Hop16Args& a, int mode, hipStream_t s);
 hipError_t launch_parity_to_h16(int kind, void* y, const d2_t* x, double scale, int nrhs, int vh, hipStream_t s);
 hipError_t launch_parity_from_h16(int kind, d2_t* y, const void* x, double scale, int nrhs, int vh, hipStream_t s);
-hipError_t launch_h16_to_f32(int kind, void* y, const void* x, float scale, int nrhs, int vh, hipStream_t s);
+hipError_t launch_h16_to_f32(int kind, void* y, const void* x, float scale, int nrhs, int vh, hipStream_t s, d2_t* z = nullptr);
+// v = a w (v may be w), b16 = sb v, x16 = sx v
+hipError_t launch_scale_to_h16(int kind, d2_t* v, const d2_t* w, double a, void* b16, double sb, void* x16, double sx, int vh,
+                               hipStream_t s);
 hipError_t launch_links_to_h16(int kind, const d2_t* in, void* out, int vh, hipStream_t s);
 hipError_t launch_clover_to_h16(int kind, const d2_t* in, void* out, int vh, hipStream_t s);
 
@@ -225,11 +228,17 @@ hipError_t launch_clover_full(const Geo& g, int parity, int nrhs, const d2_t* cl
 // FP64 vector kernels (complex128 vectors of n elements)
 hipError_t launch_dot_partial(const d2_t* V, long long vstride, int k, const d2_t* w, long long n,
                               d2_t* partial, int nbx, hipStream_t s);
-hipError_t launch_reduce_partial(const d2_t* partial, int nbx, int k, d2_t* out, hipStream_t s);
+// (host: unless null, a pinned host copy of the result, readable after a synchronisation)
+hipError_t launch_reduce_partial(const d2_t* partial, int nbx, int k, d2_t* out, d2_t* host, hipStream_t s);
 hipError_t launch_update(d2_t* w, const d2_t* V, long long vstride, int k, const d2_t* h,
                          double sign, long long n, hipStream_t s);
 hipError_t launch_norm2_partial(const d2_t* w, long long n, double* partial, int nbx, hipStream_t s);
-hipError_t launch_reduce_real(const double* partial, int nbx, double* out, hipStream_t s);
+hipError_t launch_reduce_real(const double* partial, int nbx, double* out, double* host, hipStream_t s);
+// launch_update and |w|^2 after it (partial: nbx doubles)
+hipError_t launch_update_norm(d2_t* w, const d2_t* V, long long vstride, int k, const d2_t* h, double sign, long long n,
+                              double* partial, int nbx, double* norm2, double* host, hipStream_t s);
+// v = a w (v may be w), b32 its FP32 form, x32 = omega b32 unless null
+hipError_t launch_scale_to_f32(d2_t* v, const d2_t* w, double a, void* b32, void* x32, float omega, int vh, hipStream_t s);
 hipError_t launch_scale(d2_t* out, const d2_t* in, double a, long long n, hipStream_t s);
 hipError_t launch_scale_dev(d2_t* out, const d2_t* in, const double* inv_norm_dev, long long n,
                             hipStream_t s);

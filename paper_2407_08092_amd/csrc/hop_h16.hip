@@ -260,6 +260,28 @@ __global__ void k_parity_to_h16(u4_t* __restrict__ y, const d2_t* __restrict__ x
   y[t] = pack4<S>(c);
 }
 
+// v = a w (FP64 parity vectors; v may be w) and its 16-bit forms b16 = sb v, x16 = sx v: a new
+// Krylov vector with what its preconditioner starts from, w read once
+template <typename S>
+__global__ void __launch_bounds__(256) k_scale_to_h16(d2_t* v, const d2_t* w, double a, u4_t* __restrict__ b16, double sb,
+                                                      u4_t* __restrict__ x16, double sx, int vh) {
+  const int t = (int)(blockIdx.x * 256 + threadIdx.x);  // (element row, site)
+  if (t >= SP16_E * vh) return;
+  const int e = t / vh, i = t - e * vh;
+  cpx<float> b[4], x[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const size_t at = (size_t)(4 * e + j) * vh + i;
+    const d2_t q = w[at] * a;
+    v[at] = q;
+    store_fence();
+    b[j] = {(float)(q.x * sb), (float)(q.y * sb)};
+    x[j] = {(float)(q.x * sx), (float)(q.y * sx)};
+  }
+  b16[t] = pack4<S>(b);
+  x16[t] = pack4<S>(x);
+}
+
 template <typename S>
 __global__ void k_parity_from_h16(d2_t* __restrict__ y, const u4_t* __restrict__ x, double scale, long long n3,
                                   int vh) {
@@ -282,9 +304,11 @@ __global__ void k_parity_from_h16(d2_t* __restrict__ y, const u4_t* __restrict__
   }
 }
 
-// 16-bit [nrhs][3][vh] -> FP32 paired [nrhs][6][vh] (rows 2m, 2m+1), times scale
+// 16-bit [nrhs][3][vh] -> FP32 paired [nrhs][6][vh] (rows 2m, 2m+1), times scale; and the same
+// numbers in FP64 parity vectors z unless null
 template <typename S>
-__global__ void k_h16_to_f32(f4_t* __restrict__ y, const u4_t* __restrict__ x, float scale, long long n3, int vh) {
+__global__ void k_h16_to_f32(f4_t* __restrict__ y, const u4_t* __restrict__ x, float scale, long long n3, int vh,
+                             d2_t* __restrict__ z) {
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n3) return;
   const int i = (int)(t % vh);
@@ -302,6 +326,11 @@ __global__ void k_h16_to_f32(f4_t* __restrict__ y, const u4_t* __restrict__ x, f
     o.z = c[2 * h + 1].r * scale;
     o.w = c[2 * h + 1].i * scale;
     yr[(size_t)(2 * e + h) * vh + i] = o;
+    if (z) {
+      d2_t* zr = z + rhs * 12LL * vh;
+      zr[(size_t)(4 * e + 2 * h) * vh + i] = d2_t{o.x, o.y};
+      zr[(size_t)(4 * e + 2 * h + 1) * vh + i] = d2_t{o.z, o.w};
+    }
     store_fence();
   }
 }
@@ -362,6 +391,16 @@ hipError_t launch_parity_to_h16(int kind, void* y, const d2_t* x, double scale, 
   return hipGetLastError();
 }
 
+hipError_t launch_scale_to_h16(int kind, d2_t* v, const d2_t* w, double a, void* b16, double sb, void* x16, double sx, int vh,
+                               hipStream_t s) {
+  const long long n = (long long)SP16_E * vh;
+  if (kind == H16_BF16)
+    hipLaunchKernelGGL(k_scale_to_h16<__bf16>, DDQ_H16_GRID(n), 0, s, v, w, a, (u4_t*)b16, sb, (u4_t*)x16, sx, vh);
+  else
+    hipLaunchKernelGGL(k_scale_to_h16<_Float16>, DDQ_H16_GRID(n), 0, s, v, w, a, (u4_t*)b16, sb, (u4_t*)x16, sx, vh);
+  return hipGetLastError();
+}
+
 hipError_t launch_parity_from_h16(int kind, d2_t* y, const void* x, double scale, int nrhs, int vh, hipStream_t s) {
   const long long n3 = (long long)SP16_E * vh * nrhs;
   if (kind == H16_BF16)
@@ -371,12 +410,12 @@ hipError_t launch_parity_from_h16(int kind, d2_t* y, const void* x, double scale
   return hipGetLastError();
 }
 
-hipError_t launch_h16_to_f32(int kind, void* y, const void* x, float scale, int nrhs, int vh, hipStream_t s) {
+hipError_t launch_h16_to_f32(int kind, void* y, const void* x, float scale, int nrhs, int vh, hipStream_t s, d2_t* z) {
   const long long n3 = (long long)SP16_E * vh * nrhs;
   if (kind == H16_BF16)
-    hipLaunchKernelGGL(k_h16_to_f32<__bf16>, DDQ_H16_GRID(n3), 0, s, (f4_t*)y, (const u4_t*)x, scale, n3, vh);
+    hipLaunchKernelGGL(k_h16_to_f32<__bf16>, DDQ_H16_GRID(n3), 0, s, (f4_t*)y, (const u4_t*)x, scale, n3, vh, z);
   else
-    hipLaunchKernelGGL(k_h16_to_f32<_Float16>, DDQ_H16_GRID(n3), 0, s, (f4_t*)y, (const u4_t*)x, scale, n3, vh);
+    hipLaunchKernelGGL(k_h16_to_f32<_Float16>, DDQ_H16_GRID(n3), 0, s, (f4_t*)y, (const u4_t*)x, scale, n3, vh, z);
   return hipGetLastError();
 }
 

@@ -189,7 +189,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof
 hop_split_kernel(SplitArgs a) {
   using R = typename P::R;
   __shared__ cpx<R> hs[8][6][64];
-  __shared__ cpx<R> ex[MODE == M_HOP_CLINV || MODE == M_RECON ? 12 : 1][64];
+  __shared__ cpx<R> ex[MODE == M_PREP ? 1 : 12][64];  // what the clover block acts on: the hopping term, or x
   constexpr bool FULL = MODE == M_RECON || MODE == M_PREP;
   __shared__ u4_t rows[FULL ? SPINOR_ROWS : 1][FULL_ROW];
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
@@ -223,13 +223,15 @@ hop_split_kernel(SplitArgs a) {
   const Spinor<R> pf = P::spinor(in, voff(jf)), pb = P::spinor(in, voff(jb));
   Link<R> uf, ub;
   P::links(bfield((const char*)a.links + (size_t)w * P::LK_E * field_vh(vh) * 16, P::LK_E, vh), boff(i, P::LK_E), uf, ub);
-  // the epilogue's own-site vectors: x of both spins of the clover block, b of spin w
+  // x of spin w; the other spin of its clover block comes through ex, so no wavefront reads rows
+  // that another one stores (out may be x)
   const int blk = w >> 1;
-  cpx<R> xs[6], bs[3];
-  if constexpr (MODE == M_APPLY || MODE == M_RICH || MODE == M_RESID) {
+  constexpr bool CX = MODE == M_APPLY || MODE == M_RICH || MODE == M_RESID;
+  cpx<R> xs[3], bs[3];
+  if constexpr (CX) {
     const Field xv = vec(a.x);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) xs[k] = P::row(xv, 6 * blk + k, off);
+    for (int c = 0; c < 3; ++c) xs[c] = P::row(xv, 3 * w + c, off);
   }
   {
     Half<R> hf, hb;
@@ -245,6 +247,9 @@ hop_split_kernel(SplitArgs a) {
       hs[2 * w + 1][k][lane] = hb.c[k / 3][k % 3];
     }
   }
+  if constexpr (CX)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) ex[3 * w + c][lane] = xs[c];
   if constexpr (MODE == M_RICH || MODE == M_RESID) {
     const Field bv = vec(a.b);
 #pragma unroll
@@ -252,10 +257,6 @@ hop_split_kernel(SplitArgs a) {
   }
   cpx<R> sl[18];
   if constexpr (MODE != M_PREP) P::slots(bfield(a.clov, P::CL_E, vh), boff(i, P::CL_E), blk, sl);
-  // out may be x: both wavefronts of a block have their rows of them before either stores
-  if constexpr (MODE == M_APPLY || MODE == M_RICH || MODE == M_RESID)
-#pragma unroll
-    for (int k = 0; k < 6; ++k) asm volatile("" : "+v"(xs[k].r), "+v"(xs[k].i)::"memory");
   __syncthreads();
   cpx<R> h[3] = {{R(0), R(0)}, {R(0), R(0)}, {R(0), R(0)}};
   switch (w) {
@@ -274,30 +275,26 @@ hop_split_kernel(SplitArgs a) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) o[c] = bs[c] + h[c];
   } else {
-    cpx<R> v6[6];
-    if constexpr (MODE == M_HOP_CLINV || MODE == M_RECON) {
+    if constexpr (!CX) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
         if constexpr (MODE == M_RECON) h[c] = bs[c] + h[c];
         ex[3 * w + c][lane] = h[c];
       }
       __syncthreads();
-#pragma unroll
-      for (int k = 0; k < 6; ++k) v6[k] = ex[6 * blk + k][lane];
-    } else {
-#pragma unroll
-      for (int k = 0; k < 6; ++k) v6[k] = xs[k];
     }
+    cpx<R> v6[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) v6[k] = ex[6 * blk + k][lane];
     if (w & 1)
       clover_rows<1, R>(sl, v6, o);
     else
       clover_rows<0, R>(sl, v6, o);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      const cpx<R> xo = (w & 1) ? v6[3 + c] : v6[c];
       if constexpr (MODE == M_APPLY) o[c] = o[c] - h[c];
       if constexpr (MODE == M_RESID) o[c] = bs[c] - o[c] + h[c];
-      if constexpr (MODE == M_RICH) o[c] = xo + (R)a.omega * (bs[c] - o[c] + h[c]);
+      if constexpr (MODE == M_RICH) o[c] = ex[3 * w + c][lane] + (R)a.omega * (bs[c] - o[c] + h[c]);
     }
   }
   if constexpr (MODE == M_RECON) {
@@ -365,8 +362,8 @@ static hipError_t split_launch(SplitArgs a, int mode, hipStream_t s) {
 //     so fewer of them no longer help L2);
 //   several: the wavefronts of one 64-site group follow each other and take links and clover
 //     from L2; FP32 (no tile set) at every size measured, 2 right-hand sides on 32^3 x 64 889 ->
-//     723, 5 on 24^3 x 48 700 -> 487; FP64 from 3 on, 5 on 32^3 x 64 4466 -> 3375, with 2 16^3 x 32
-//     110 -> 90 but 28^3 x 56 890 -> 939;
+//     723, 5 on 24^3 x 48 700 -> 487; FP64 from 3 on, 5 on 32^3 x 64 4466 -> 3120, with 2 16^3 x 32
+//     110 -> 76 but 28^3 x 56 890 -> 939;
 //   16 bits: 65,536 sites (16^3 x 32 20 -> 17), 20^3 x 32 (128,000) 25 -> 28; three right-hand
 //     sides 16^4 15 -> 11, 16^3 x 32 16 -> 19 (the one-thread kernel shares a link among three).
 bool hop_split_takes(const Geo& g, int bytes_per_complex, int nrhs) {
