@@ -285,21 +285,96 @@ __global__ void __launch_bounds__(SAP_HALF) k_sap_block(SapArgs a) {
 // A x - 1/2 sum over the 8 hops of (1 -/+ g_mu) U x(neighbour) with the lattice's
 // boundary conditions, the neighbours anywhere in the lattice.  Links and clover blocks
 // (A_ee, A_oo: the undivided blocks) come from FP64 copies in SAP order, so each
-// wavefront reads them as contiguous runs; x, b and r are the full vectors.  The
+// wavefront reads them as contiguous runs; x, b and r are the full vectors.  The block's
+// own x, three quarters of what the hops read, is staged in LDS by contiguous loads: read
+// from the full vector (16 bytes a lane, 384 apart) a wavefront's spinors outgrow the L1
+// and come again from L2 (19 M requests a launch at 24^3 x 48, staged 11 M).  A sweep with
+// FP32 blocks 532 -> 507 us, 32^3 x 64 1563 -> 1413, 8^4 119 -> 108; FP64 830 -> 789.  What
+// is left past L2, 1.24 GB a launch at 24^3 x 48, takes 200 us at 6.2 TB/s.  The
 // on-chip block solves form it in their prologue; k_sap_residual writes it out for the
 // other block-solve kernel.
 // ---------------------------------------------------------------------------
-// r at the site (parity q, half index j) of block blk at block coordinates bc
+// The block's sites of a full vector are 64 runs of 48 elements (4 sites x 12 rows, 16
+// bytes each).  In LDS: element row k of the site (parity q, half index j) at
+// (12 q + k) * SAP_XP + j; the pitch of 129 spreads a run's rows over the banks.
+constexpr int SAP_XP = SAP_HALF + 1;
+constexpr int SAP_X_E = 24 * SAP_XP;             // elements of a block's vector in LDS
+constexpr int SAP_BLOCK_E = 2 * SAP_HALF * 12;   // elements of a block in a full vector
+
+// element e (of SAP_BLOCK_E) of block bc: its position in the full vector, and in LDS
+__device__ __forceinline__ long long sap_block_elem(const Geo& g, const int bc[4], int e, int& at) {
+  const int run = e / 48, off = e - 48 * run, sx = off / 12, k = off - 12 * sx;
+  const int y = run & 3, z = (run >> 2) & 3, t = run >> 4;
+  const int q = (sx + y + z + t) & 1;
+  at = (12 * q + k) * SAP_XP + ((sx >> 1) + 2 * run);
+  const long long row = (SAP_B * bc[1] + y) + (long long)g.L[1] * ((SAP_B * bc[2] + z) + (long long)g.L[2] * (SAP_B * bc[3] + t));
+  return (SAP_B * bc[0] + (long long)g.L[0] * row) * 12 + off;
+}
+
+// the block's sites of the full vector x into LDS, by 256 threads; a barrier must follow
+__device__ __forceinline__ void sap_stage_block(const Geo& g, const int bc[4], const d2_t* x, d2_t* xs) {
+  constexpr int N = SAP_BLOCK_E / 256;
+  d2_t v[N];
+  int at[N];
+#pragma unroll
+  for (int n = 0; n < N; ++n) v[n] = x[sap_block_elem(g, bc, (int)threadIdx.x + 256 * n, at[n])];
+#pragma unroll
+  for (int n = 0; n < N; ++n) xs[at[n]] = v[n];
+}
+
+// x at hop H's neighbour of the site at local coordinates lc, lattice coordinates gc:
+// from the staged block, or from the full vector where it lies outside (or across the
+// lattice boundary of a block that spans the direction)
+template <int H>
+__device__ __forceinline__ Spinor<double> sap_residual_nbr(const Geo& g, const int lc[4], const int gc[4], int q,
+                                                           const d2_t* x, const d2_t* xs) {
+  constexpr int mu = H >> 1;
+  int nl[4] = {lc[0], lc[1], lc[2], lc[3]};
+  nl[mu] += (H & 1) ? -1 : 1;
+  Spinor<double> p;
+  if ((unsigned)nl[mu] < (unsigned)SAP_B) {
+    const int jn = (nl[0] + SAP_B * (nl[1] + SAP_B * (nl[2] + SAP_B * nl[3]))) >> 1;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+      const d2_t v = xs[(12 * (1 - q) + k) * SAP_XP + jn];
+      p.c[k / 3][k % 3] = {v.x, v.y};
+    }
+  } else {
+    int nc[4] = {gc[0], gc[1], gc[2], gc[3]};
+    nc[mu] += (H & 1) ? -1 : 1;
+    if (nc[mu] < 0) nc[mu] += g.L[mu];
+    if (nc[mu] >= g.L[mu]) nc[mu] -= g.L[mu];
+    p = sap_load_full<double>(x, nc[0] + (long long)g.L[0] * (nc[1] + (long long)g.L[1] * (nc[2] + (long long)g.L[2] * nc[3])));
+  }
+  return p;
+}
+
+// hops H..7; the link of hop H + 1 is on its way during hop H
+template <int H>
+__device__ __forceinline__ void sap_residual_hops(const Geo& g, const int lc[4], const int gc[4], int q,
+                                                  const d2_t* x, const d2_t* xs, const HopCtx<double>& c,
+                                                  Spinor<double>& acc, const Link<double>& u) {
+  const Spinor<double> p = sap_residual_nbr<H>(g, lc, gc, q, x, xs);
+  if constexpr (H < 7) {
+    const Link<double> un = load_link_half<double>(link_field(c, (H + 1) >> 1), (H + 1) & 1, c.loff);
+    hop_compute<H, double>(acc, p, u, c);
+    hop_fence<double>(acc);
+    sap_residual_hops<H + 1>(g, lc, gc, q, x, xs, c, acc, un);
+  } else {
+    hop_compute<H, double>(acc, p, u, c);
+    hop_fence<double>(acc);
+  }
+}
+
+// r at the site (parity q, half index j) of block blk at block coordinates bc; xs: the
+// block's x, staged
 __device__ __forceinline__ Spinor<double> sap_residual_site(const Geo& g, const int bc[4], int blk, int q, int j,
-                                                            const d2_t* b, const d2_t* x, const void* links,
-                                                            const void* clov) {
+                                                            const d2_t* b, const d2_t* x, const d2_t* xs,
+                                                            const void* links, const void* clov) {
   int lc[4], gc[4];
   sap_local(j, q, lc);
   for (int mu = 0; mu < 4; ++mu) gc[mu] = SAP_B * bc[mu] + lc[mu];
-  auto lex = [&](const int c[4]) {
-    return c[0] + (long long)g.L[0] * (c[1] + (long long)g.L[1] * (c[2] + (long long)g.L[2] * c[3]));
-  };
-  const long long site = lex(gc);
+  const long long site = gc[0] + (long long)g.L[0] * (gc[1] + (long long)g.L[1] * (gc[2] + (long long)g.L[2] * gc[3]));
   const int ss = blk * SAP_HALF + j;
   HopCtx<double> c;
   c.links = (const pair<double>*)links;
@@ -310,36 +385,16 @@ __device__ __forceinline__ Spinor<double> sap_residual_site(const Geo& g, const 
   c.sb = 1.0;
   c.nb.sgn_tf = (g.antiperiodic && gc[3] == g.L[3] - 1) ? -1.f : 1.f;
   c.nb.sgn_tb = (g.antiperiodic && gc[3] == 0) ? -1.f : 1.f;
-  long long nsite[8];
-#pragma unroll
-  for (int H = 0; H < 8; ++H) {
-    const int mu = H >> 1;
-    int nc[4] = {gc[0], gc[1], gc[2], gc[3]};
-    nc[mu] += (H & 1) ? -1 : 1;
-    if (nc[mu] < 0) nc[mu] += g.L[mu];
-    if (nc[mu] >= g.L[mu]) nc[mu] -= g.L[mu];
-    nsite[H] = lex(nc);
-  }
   Spinor<double> acc;
   zero(acc);
+  sap_residual_hops<0>(g, lc, gc, q, x, xs, c, acc, load_link_half<double>(link_field(c, 0), 0, c.loff));
+  Spinor<double> own;
 #pragma unroll
-  for (int H = 0; H < 8; ++H) {
-    const Spinor<double> p = sap_load_full<double>(x, nsite[H]);
-    const Link<double> u = load_link_half<double>(link_field(c, H >> 1), H & 1, c.loff);
-    switch (H) {
-      case 0: hop_compute<0, double>(acc, p, u, c); break;
-      case 1: hop_compute<1, double>(acc, p, u, c); break;
-      case 2: hop_compute<2, double>(acc, p, u, c); break;
-      case 3: hop_compute<3, double>(acc, p, u, c); break;
-      case 4: hop_compute<4, double>(acc, p, u, c); break;
-      case 5: hop_compute<5, double>(acc, p, u, c); break;
-      case 6: hop_compute<6, double>(acc, p, u, c); break;
-      default: hop_compute<7, double>(acc, p, u, c); break;
-    }
-    hop_fence<double>(acc);
+  for (int k = 0; k < 12; ++k) {
+    const d2_t v = xs[(12 * q + k) * SAP_XP + j];
+    own.c[k / 3][k % 3] = {v.x, v.y};
   }
-  const Spinor<double> ax =
-      clover_mul<double>(bfield(clov, CLOVER_ROWS, g.Vh), boff(ss, CLOVER_ROWS), sap_load_full<double>(x, site));
+  const Spinor<double> ax = clover_mul<double>(bfield(clov, CLOVER_ROWS, g.Vh), boff(ss, CLOVER_ROWS), own);
   const Spinor<double> bb = sap_load_full<double>(b, site);
   Spinor<double> r;
 #pragma unroll
@@ -373,11 +428,14 @@ struct SapResArgs {
 
 // one workgroup of 256 threads per block (thread t: parity t / 128, half index t mod 128)
 __global__ void __launch_bounds__(256) k_sap_residual(SapResArgs a) {
+  __shared__ d2_t xs[SAP_X_E];
   int bc[4], blk;
   if (!sap_colour_block(a.nb, a.colour, (int)blockIdx.x, bc, blk)) return;  // uniform
+  sap_stage_block(a.g, bc, a.src.x, xs);
+  __syncthreads();
   // the parity is uniform over a wavefront: its links and clover through scalar descriptors
   const int q = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 7), j = (int)threadIdx.x & (SAP_HALF - 1);
-  const Spinor<double> r = sap_residual_site(a.g, bc, blk, q, j, a.src.b, a.src.x, a.src.links[q], a.src.clov[q]);
+  const Spinor<double> r = sap_residual_site(a.g, bc, blk, q, j, a.src.b, a.src.x, xs, a.src.links[q], a.src.clov[q]);
   int lc[4], gc[4];
   sap_local(j, q, lc);
   for (int mu = 0; mu < 4; ++mu) gc[mu] = SAP_B * bc[mu] + lc[mu];
@@ -600,7 +658,9 @@ __device__ __forceinline__ void sap_sum3_4(double v[3], double* red /* [4][3] */
 template <typename R, bool L18, bool RES>
 __global__ void __launch_bounds__(SAP_SPLIT) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 2 : 1)))
 k_sap_block_split(SapArgs a) {
-  __shared__ cpx<R> lk[L18 ? 9 * SAP_L18 : SAP_LK * 8 * SAP_HALF];  // the block's links
+  // the block's links; before them the block's x (RES)
+  constexpr int LK_N = L18 ? 9 * SAP_L18 : SAP_LK * 8 * SAP_HALF, XS_N = SAP_X_E * 16 / (int)sizeof(cpx<R>);
+  __shared__ __attribute__((aligned(16))) cpx<R> lk[RES && XS_N > LK_N ? XS_N : LK_N];
   __shared__ cpx<R> vb[12][SAP_HALF + 1];  // hop input; column SAP_HALF zero
   __shared__ cpx<R> xb[L18 ? 1 : 12][SAP_HALF];  // partial sums in exchange (12-real form)
   __shared__ double red[12];
@@ -629,8 +689,12 @@ k_sap_block_split(SapArgs a) {
     cpx<R>* rs = lk;  // [parity][12 rows][128 sites]
     {
       const int q = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 7);  // uniform over a wavefront
+      d2_t* xs = (d2_t*)lk;
+      sap_stage_block(g, bc, a.res.x, xs);
+      __syncthreads();
       const Spinor<double> rv =
-          sap_residual_site(g, bc, blk, q, j, a.res.b, a.res.x, a.res.links[q], a.res.clov[q]);
+          sap_residual_site(g, bc, blk, q, j, a.res.b, a.res.x, xs, a.res.links[q], a.res.clov[q]);
+      __syncthreads();  // rs overwrites xs
 #pragma unroll
       for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
