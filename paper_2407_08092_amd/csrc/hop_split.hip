@@ -355,22 +355,26 @@ static hipError_t split_launch(SplitArgs a, int mode, hipStream_t s) {
 }
 
 // Where four threads a site beat one (microseconds a sweep, one thread -> four):
-//   FP64, one right-hand side: latency-bound launches only; 8^4 31 -> 11, 16^4 42 -> 30, but
-//     16^3 x 24 (49,152 sites) 41 -> 42: a workgroup's 61 KB of LDS leave two on a compute unit;
+//   FP64, one right-hand side: latency-bound launches only; 8^4 31 -> 11, 16^4 42 -> 30.
+//     Repeated sweeps gain up to 200,000 sites (20^3 x 32 114 -> 95), but a lone apply that
+//     finds its fields in no cache does not (28^3 x 16 145 -> 152; applies after set_gauge
+//     and set_clover on 16^3 x 32 cost 10 more), and above that repeated ones depend on the
+//     shape (28^3 x 24 230 -> 217, 28^3 x 32 289 -> 316);
 //   FP32, one: up to 400,000 sites; 8^4 19 -> 9, 16^3 x 32 31 -> 27, 24^3 x 48 (331,776) 142 -> 124,
 //     while 32^4 (524,288) 203 -> 205 (a t-slice's share per XCD has outgrown the sites in flight,
-//     so fewer of them no longer help L2);
+//     so fewer of them no longer help L2); with the fields in no cache 16^3 x 32 36 -> 35,
+//     24^3 x 32 103 -> 103, 24^3 x 48 150 -> 144;
 //   several: the wavefronts of one 64-site group follow each other and take links and clover
 //     from L2; FP32 (no tile set) at every size measured, 2 right-hand sides on 32^3 x 64 889 ->
-//     723, 5 on 24^3 x 48 700 -> 487; FP64 from 3 on, 5 on 32^3 x 64 4466 -> 3120, with 2 16^3 x 32
-//     110 -> 76 but 28^3 x 56 890 -> 939;
+//     723, 5 on 24^3 x 48 700 -> 487; FP64 too, 2 on 24^3 x 48 498 -> 469, on 32^4 760 -> 752 and on
+//     40^3 x 64 3220 -> 2919, 5 on 32^3 x 64 4466 -> 3120;
 //   16 bits: 65,536 sites (16^3 x 32 20 -> 17), 20^3 x 32 (128,000) 25 -> 28; three right-hand
 //     sides 16^4 15 -> 11, 16^3 x 32 16 -> 19 (the one-thread kernel shares a link among three).
 bool hop_split_takes(const Geo& g, int bytes_per_complex, int nrhs) {
   const long long n = (long long)g.Vh * nrhs;
   if (bytes_per_complex == 4) return n <= (nrhs == 1 ? 65536 : 98304);
   if (bytes_per_complex == 8) return nrhs > 1 || n <= 400000;
-  return nrhs > 2 || n <= (nrhs == 1 ? 40960 : 200000);
+  return nrhs > 1 || n <= 40960;
 }
 
 template <typename R, bool L12>
