@@ -111,37 +111,55 @@ hipError_t launch_pack_gauge(const Geo& g, const d2_t* U, d2_t* out_e, d2_t* out
 // ---------------------------------------------------------------------------
 // clover blocks
 // ---------------------------------------------------------------------------
-// F_munu(x) of plane (mu, nu) from Q = the four leaves, F = (Q - Q^H) / 8.  With
-//   S = U_nu(x+mu) U_mu(x+nu)^H U_nu(x)^H - U_nu(x+mu-nu)^H U_mu(x-nu)^H U_nu(x-nu),
-//   X = U_nu(x) U_mu(x-mu+nu)^H U_nu(x-mu)^H - U_nu(x-nu)^H U_mu(x-mu-nu)^H U_nu(x-mu-nu)
-// the leaves 1 and 4 are U_mu(x) S and leaves 2 and 3 X U_mu(x-mu), up to Hermitian
-// conjugates that Q - Q^H cancels: Q - Q^H = T - T^H, T = U_mu(x) S + X U_mu(x-mu).
+// F_munu(x) of plane (mu, nu): F = (Q - Q^H) / 8 with Q the sum of the four leaves
+//   U_mu(x) U_nu(x+mu) U_mu(x+nu)^H U_nu(x)^H,          U_nu(x) U_mu(x-mu+nu)^H U_nu(x-mu)^H U_mu(x-mu),
+//   U_mu(x-mu)^H U_nu(x-mu-nu)^H U_mu(x-mu-nu) U_nu(x-nu),  U_nu(x-nu)^H U_mu(x-nu) U_nu(x+mu-nu) U_mu(x)^H,
+// each a chain from the left, 12 products.  10 would do (leaves 1 and 4, 2 and 3 share a factor up
+// to conjugates that Q - Q^H cancels; 97 us against 119 for the clover build on 16^3 x 32), but their
+// last bits differ, and a block entry whose FP32 rounding turns over moves everything that is solved
+// with the FP32 blocks by 1e-9 to 1e-8.
 __device__ __forceinline__ AH3 field_strength(const PackedLinks& L, const Geo& g, const Site& s, int p, int mu, int nu) {
   const int o = 1 - p;
   const Site fm = site_shift(g, s, mu, 1), fn = site_shift(g, s, nu, 1);
   const Site bm = site_shift(g, s, mu, -1), bn = site_shift(g, s, nu, -1);
   auto U = [&](int q, int dir, int i) { return packed_link(L, g, q, dir, i); };
+  // X = X B, the sums of c3_mul, row by row
+  auto times = [](C3& X, const C3& B) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      cpx<double> row[3];
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        row[b] = X.a[a][0] * B.a[0][b];
+        cfma(row[b], X.a[a][1], B.a[1][b]);
+        cfma(row[b], X.a[a][2], B.a[2][b]);
+      }
+#pragma unroll
+      for (int b = 0; b < 3; ++b) X.a[a][b] = row[b];
+    }
+    c3_fence(X);
+  };
+  const int i0 = s.i, bb = site_shift(g, bm, nu, -1).i, fb = site_shift(g, fm, nu, -1).i;  // x, x-mu-nu, x+mu-nu
   // one product at a time (c3_fence): the matrices in flight fit the registers of three wavefronts
-  C3 A = c3_mul_dag(U(o, nu, fm.i), U(o, mu, fn.i));
-  c3_fence(A);
-  C3 S = c3_mul_dag(A, U(p, nu, s.i));
-  c3_fence(S);
-  A = c3_mul(U(o, mu, bn.i), U(p, nu, site_shift(g, fm, nu, -1).i));
-  c3_fence(A);
-  S = c3_sub(S, c3_dag_mul(A, U(o, nu, bn.i)));
-  c3_fence(S);
-  C3 T = c3_mul(U(p, mu, s.i), S);
-  c3_fence(T);
-  A = c3_mul_dag(U(p, nu, s.i), U(p, mu, site_shift(g, fn, mu, -1).i));
-  c3_fence(A);
-  S = c3_mul_dag(A, U(o, nu, bm.i));
-  c3_fence(S);
-  const int bb = site_shift(g, bm, nu, -1).i;  // x-mu-nu
-  A = c3_mul(U(p, mu, bb), U(o, nu, bn.i));
-  c3_fence(A);
-  S = c3_sub(S, c3_dag_mul(A, U(p, nu, bb)));
-  c3_fence(S);
-  T = c3_add(T, c3_mul(S, U(o, mu, bm.i)));
+  C3 T = U(p, mu, i0);
+  times(T, U(o, nu, fm.i));
+  times(T, c3_dag(U(o, mu, fn.i)));
+  times(T, c3_dag(U(p, nu, i0)));
+  C3 X = U(p, nu, i0);
+  times(X, c3_dag(U(p, mu, site_shift(g, fn, mu, -1).i)));
+  times(X, c3_dag(U(o, nu, bm.i)));
+  times(X, U(o, mu, bm.i));
+  T = c3_add(T, X);
+  X = c3_dag(U(o, mu, bm.i));
+  times(X, c3_dag(U(p, nu, bb)));
+  times(X, U(p, mu, bb));
+  times(X, U(o, nu, bn.i));
+  T = c3_add(T, X);
+  X = c3_dag(U(o, nu, bn.i));
+  times(X, U(o, mu, bn.i));
+  times(X, U(p, nu, fb));
+  times(X, c3_dag(U(p, mu, i0)));
+  T = c3_add(T, X);
   AH3 F;
 #pragma unroll
   for (int a = 0; a < 3; ++a) F.d[a] = 0.25 * T.a[a][a].i;
@@ -173,38 +191,50 @@ __device__ __forceinline__ void store_packed(void* C, int blk, int i, int vh, co
 
 // Inverse of a Hermitian positive-definite 6x6 matrix by Cholesky A = L L^H: reads and writes A's
 // diagonal and upper triangle, L, L^-1 and the products in place below it; returns false if a
-// pivot is not positive.
-__device__ __forceinline__ bool hpd_inverse6(cpx<double> (&A)[6][6]) {
+// pivot is not positive.  Y: A's upper triangle before its factor h; the first term of a sum
+// takes h Y unrounded where it can.  The fused operations are written out, so that every
+// build gives the same bits.
+__device__ __forceinline__ bool hpd_inverse6(cpx<double> (&A)[6][6], const cpx<double> (&Y)[6][6], double h) {
   bool ok = true;
-  double inv[6];  // 1 / L_jj
+  double dg[6];  // L_jj
 #pragma unroll
   for (int j = 0; j < 6; ++j) {
     double d = A[j][j].r;
 #pragma unroll
-    for (int k = 0; k < j; ++k) d -= A[j][k].r * A[j][k].r + A[j][k].i * A[j][k].i;
+    for (int k = 0; k < j; ++k) {
+      const double x = A[j][k].r, y = A[j][k].i;
+      d -= fma(y, y, x * x);
+    }
     if (!(d > 0.0)) {
       ok = false;
       d = 1.0;
     }
-    inv[j] = 1.0 / sqrt(d);
+    dg[j] = sqrt(d);
 #pragma unroll
     for (int r = j + 1; r < 6; ++r) {
       cpx<double> s = conj(A[j][r]);
 #pragma unroll
-      for (int k = 0; k < j; ++k) s = s - A[r][k] * conj(A[j][k]);
-      A[r][j] = inv[j] * s;
+      for (int k = 0; k < j; ++k) {
+        const cpx<double> x = A[r][k], y = A[j][k];
+        const double tr = fma(x.i, y.i, x.r * y.r), ti = fma(x.i, y.r, -(x.r * y.i));
+        if (k > 0) s = {s.r - tr, s.i - ti};
+        else s = {j < 3 && r >= 3 ? fma(h, Y[j][r].r, -tr) : s.r - tr, fma(h, -Y[j][r].i, -ti)};
+      }
+      A[r][j] = {s.r / dg[j], s.i / dg[j]};
     }
     __builtin_amdgcn_sched_barrier(0);
   }
-  // L^-1 below the diagonal, column by column from the last: column c from L^-1's rows and columns > c
+  // L^-1 in its place, column by column: column c needs L's rows from column c on
+  double inv[6];
 #pragma unroll
-  for (int c = 4; c >= 0; --c) {
+  for (int c = 0; c < 6; ++c) {
+    inv[c] = 1.0 / dg[c];
 #pragma unroll
-    for (int r = 5; r > c; --r) {
-      cpx<double> s = inv[r] * A[r][c];
+    for (int r = c + 1; r < 6; ++r) {
+      cpx<double> s = {A[r][c].r * inv[c], A[r][c].i * inv[c]};
 #pragma unroll
       for (int k = c + 1; k < r; ++k) cfma(s, A[r][k], A[k][c]);
-      A[r][c] = {-s.r * inv[c], -s.i * inv[c]};
+      A[r][c] = {-s.r / dg[r], -s.i / dg[r]};
     }
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -213,7 +243,7 @@ __device__ __forceinline__ bool hpd_inverse6(cpx<double> (&A)[6][6]) {
   for (int j = 0; j < 6; ++j) {
     double d = inv[j] * inv[j];
 #pragma unroll
-    for (int r = j + 1; r < 6; ++r) d = fma(A[r][j].r, A[r][j].r, fma(A[r][j].i, A[r][j].i, d));
+    for (int r = j + 1; r < 6; ++r) d = fma(A[r][j].i, A[r][j].i, fma(A[r][j].r, A[r][j].r, d));
     A[j][j] = {d, 0.0};
 #pragma unroll
     for (int k = j + 1; k < 6; ++k) {
@@ -236,7 +266,7 @@ __device__ __forceinline__ bool hpd_inverse6(cpx<double> (&A)[6][6]) {
 // from which two wavefronts (one per block) form, and on odd sites invert, the 6x6 blocks.
 // Bound by the latency of the links (one product at a time, three wavefronts a SIMD): 16^3 x 32
 // 225 us (one thread a site on canonical links, 464 B of scratch, and 2 x 17 us for the FP32 copy)
-// -> 96.  Few sites in flight matter more than registers: four wavefronts with three planes each
+// -> 119.  Few sites in flight matter more than registers: four wavefronts with three planes each
 // of both parities read 506 MB past L2 against 165 here, and took the same 93 us with twice the
 // matrices in flight.
 constexpr int CLOVER_PLANES = 6;
@@ -278,17 +308,20 @@ k_clover_build(Geo g, PackedLinks L, double c_sw, double m0, ClovOut out, int* n
   const AH3 E0 = field(2, 3, 1.0), E1 = field(4, 1, -1.0), E2 = field(5, 0, 1.0);
   // M = (i h) [s1 (x) E0 + s2 (x) E1 + s3 (x) E2] + (4 + m0), spin blocks of the bracket
   // [[e2, e0 - i e1], [e0 + i e1, -e2]]: upper triangle
-  cpx<double> M[6][6];
+  cpx<double> M[6][6], Y[6][6];
 #pragma unroll
   for (int a = 0; a < 3; ++a)
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
       const cpx<double> e0 = ah_at(E0, a, b), e1 = ah_at(E1, a, b), e2 = ah_at(E2, a, b);
       if (a <= b) {
-        M[a][b] = h * times_i(e2);
+        Y[a][b] = times_i(e2);
+        M[a][b] = h * Y[a][b];
+        Y[3 + a][3 + b] = {-Y[a][b].r, -Y[a][b].i};
         M[3 + a][3 + b] = {-M[a][b].r, -M[a][b].i};
       }
-      M[a][3 + b] = h * times_i(e0 - times_i(e1));
+      Y[a][3 + b] = times_i(e0 - times_i(e1));
+      M[a][3 + b] = h * Y[a][3 + b];
     }
 #pragma unroll
   for (int k = 0; k < 6; ++k) M[k][k].r += 4.0 + m0;
@@ -297,7 +330,7 @@ k_clover_build(Geo g, PackedLinks L, double c_sw, double m0, ClovOut out, int* n
     if (out.e32) store_packed<float>(out.e32, blk, i, vh, M);  // uniform
   } else {
     store_packed<double>(out.o, blk, i, vh, M);  // A_oo itself, for the full operator
-    if (!hpd_inverse6(M)) {
+    if (!hpd_inverse6(M, Y, h)) {
       *notpd = 1;
 #pragma unroll
       for (int j = 0; j < 6; ++j)
