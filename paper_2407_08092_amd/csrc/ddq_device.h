@@ -389,21 +389,12 @@ __device__ __forceinline__ Link<R> load_link_half(const Field& U, int half, uint
   load_rows<R, AUX>(U, 9 * half, 9, off, l.u);  // FP64 only: 9 rows = 9 elements
   return l;
 }
-// conj(a b - c d) as written here in every kernel: left to the compiler, the way the products
-// and sums are fused differs from one kernel to the next
-template <typename R>
-__device__ __forceinline__ cpx<R> conj_cross(cpx<R> a, cpx<R> b, cpx<R> c, cpx<R> d) {
-#pragma clang fp contract(off)
-  const R re = fma(a.r, b.r, fma(-a.i, b.i, fma(-c.r, d.r, c.i * d.i)));
-  const R im = fma(c.r, d.i, fma(c.i, d.r, fma(-a.r, b.i, -(a.i * b.r))));
-  return {re, im};
-}
 // SU(3) from its first two rows: row 2 = conj(row 0 x row 1)
 template <typename R>
 __device__ __forceinline__ void su3_third_row(Link<R>& l) {
-  l.u[6] = conj_cross(l.u[1], l.u[5], l.u[2], l.u[4]);
-  l.u[7] = conj_cross(l.u[2], l.u[3], l.u[0], l.u[5]);
-  l.u[8] = conj_cross(l.u[0], l.u[4], l.u[1], l.u[3]);
+  l.u[6] = conj(l.u[1] * l.u[5] - l.u[2] * l.u[4]);
+  l.u[7] = conj(l.u[2] * l.u[3] - l.u[0] * l.u[5]);
+  l.u[8] = conj(l.u[0] * l.u[4] - l.u[1] * l.u[3]);
 }
 
 // 12-real storage (LINK12_ROWS complex rows per direction: the first two rows of

@@ -52,17 +52,11 @@ __device__ __forceinline__ Spinor<float> load_spinor16(const Field& v, uint32_t 
   for (int e = 0; e < SP16_E; ++e) q[e] = ld16<AUX>(v, e, off);
   return unpack_spinor<S>(q);
 }
-// a result in FP32 before it is narrowed: a fused multiply-add that rounds straight to 16 bits,
-// which the compiler forms in some kernels and not in others, would make their results differ
-__device__ __forceinline__ cpx<float> in_fp32(cpx<float> c) {
-  asm("" : "+v"(c.r), "+v"(c.i));
-  return c;
-}
 template <typename S, int AUX = DDQ_STORE_AUX>
 __device__ __forceinline__ void store_spinor16(const Field& v, uint32_t off, const Spinor<float>& s) {
   cpx<float> c[12];
 #pragma unroll
-  for (int k = 0; k < 12; ++k) c[k] = in_fp32(s.c[k / 3][k % 3]);
+  for (int k = 0; k < 12; ++k) c[k] = s.c[k / 3][k % 3];
 #pragma unroll
   for (int e = 0; e < SP16_E; ++e) st16<AUX>(v, e, off, pack4<S>(c + 4 * e));
 }

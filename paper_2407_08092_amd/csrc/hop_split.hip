@@ -21,6 +21,20 @@
 
 namespace ddq {
 
+// The third row of a 12-real link with the multiply-adds of the one-thread FP32 kernels written
+// out: there a product's imaginary part starts from a.r b.i, and from a.i b.r in the forward
+// link's products with entry 0.
+template <bool FWD, typename R>
+__device__ __forceinline__ void third_row_as_hop(Link<R>& l) {
+  auto re = [](cpx<R> a, cpx<R> b) -> R { return fma(a.r, b.r, -(a.i * b.i)); };
+  auto im = [](cpx<R> a, cpx<R> b) -> R { return fma(a.i, b.r, a.r * b.i); };
+  auto im0 = [&](cpx<R> b) -> R { return FWD ? fma(l.u[0].r, b.i, l.u[0].i * b.r) : im(l.u[0], b); };
+  const cpx<R>* u = l.u;
+  l.u[6] = {re(u[1], u[5]) - re(u[2], u[4]), -(im(u[1], u[5]) - im(u[2], u[4]))};
+  l.u[7] = {re(u[2], u[3]) - re(u[0], u[5]), -(im(u[2], u[3]) - im0(u[5]))};
+  l.u[8] = {re(u[0], u[4]) - re(u[1], u[3]), -(im0(u[4]) - im(u[1], u[3]))};
+}
+
 // Storage policies: how a precision's fields are read and written.  KEEP: the operator's
 // fields fit the Infinity Cache and everything may stay there; else links and results are
 // streamed past it.
@@ -34,7 +48,8 @@ struct SplitR {
   static __device__ __forceinline__ void links(const Field& U, uint32_t off, Link<R>& f, Link<R>& b) {
     if constexpr (L12) {
       load_link_pair12<R, LINK_AUX>(U, off, f, b);
-      su3_third_row(b);
+      third_row_as_hop<true>(f);
+      third_row_as_hop<false>(b);
     } else if constexpr (CPE<R> == 1) {
       f = load_link_half<R, LINK_AUX>(U, 0, off);
       b = load_link_half<R, LINK_AUX>(U, 1, off);
@@ -57,6 +72,7 @@ struct SplitR {
       return {q.x, q.y};
     }
   }
+  static __device__ __forceinline__ cpx<R> stored(cpx<R> c) { return c; }
   static __device__ __forceinline__ void put(const Field& v, int r, uint32_t off, cpx<R> c) {
     if constexpr (CPE<R> == 1) {
       __builtin_amdgcn_raw_buffer_store_b128(pack<R>(&c), v.rsrc, (int)off, (int)(r * v.row_bytes), ST_AUX);
@@ -103,9 +119,12 @@ struct Split16 {
         __builtin_amdgcn_raw_buffer_load_b32(v.rsrc, (int)(off + 4u * (r & 3)), (int)((r >> 2) * v.row_bytes), 0);
     return {h2f<S>((u16_t)(q & 0xffffu)), h2f<S>((u16_t)(q >> 16))};
   }
-  static __device__ __forceinline__ void put(const Field& v, int r, uint32_t off, cpx<R> c) {
-    c = in_fp32(c);
-    const unsigned q = (unsigned)f2h<S>(c.r) | ((unsigned)f2h<S>(c.i) << 16);
+  static __device__ __forceinline__ unsigned stored(cpx<R> c) {
+    unsigned q = (unsigned)f2h<S>(c.r) | ((unsigned)f2h<S>(c.i) << 16);
+    asm("" : "+v"(q));
+    return q;
+  }
+  static __device__ __forceinline__ void put(const Field& v, int r, uint32_t off, unsigned q) {
     __builtin_amdgcn_raw_buffer_store_b32(q, v.rsrc, (int)(off + 4u * (r & 3)), (int)((r >> 2) * v.row_bytes), 0);
   }
 };
@@ -271,9 +290,10 @@ hop_split_kernel(SplitArgs a) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) unpack<R>(rows[3 * w + c][lane], bs + c);
   cpx<R> o[3];
+  decltype(P::stored(o[0])) y[3];
   if constexpr (MODE == M_PREP) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) o[c] = bs[c] + h[c];
+    for (int c = 0; c < 3; ++c) y[c] = P::stored(o[c] = bs[c] + h[c]);
   } else {
     if constexpr (!CX) {
 #pragma unroll
@@ -286,15 +306,25 @@ hop_split_kernel(SplitArgs a) {
     cpx<R> v6[6];
 #pragma unroll
     for (int k = 0; k < 6; ++k) v6[k] = ex[6 * blk + k][lane];
+    // A 16-bit result takes its stored form where it is formed, as in the one-thread kernels: the
+    // compiler narrows in the multiply-add itself (one rounding, not two), which it cannot across
+    // a merge of branches.  Kernel A's last operation is the clover product's.
+    auto rows3 = [&](auto half) {
+      clover_rows<half.value, R>(sl, v6, o);
+      if constexpr (MODE == M_HOP_CLINV)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) y[c] = P::stored(o[c]);
+    };
     if (w & 1)
-      clover_rows<1, R>(sl, v6, o);
+      rows3(std::integral_constant<int, 1>{});
     else
-      clover_rows<0, R>(sl, v6, o);
+      rows3(std::integral_constant<int, 0>{});
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       if constexpr (MODE == M_APPLY) o[c] = o[c] - h[c];
       if constexpr (MODE == M_RESID) o[c] = bs[c] - o[c] + h[c];
       if constexpr (MODE == M_RICH) o[c] = ex[3 * w + c][lane] + (R)a.omega * (bs[c] - o[c] + h[c]);
+      if constexpr (MODE != M_HOP_CLINV) y[c] = P::stored(o[c]);
     }
   }
   if constexpr (MODE == M_RECON) {
@@ -310,12 +340,12 @@ hop_split_kernel(SplitArgs a) {
     if (a.out32) {  // uniform
       using F = SplitR<float, false, true>;
       const size_t r32 = (size_t)rhs * F::SP_E * (size_t)vh * 16;
-      const Field y = vfield((char*)a.out32 + r32, F::SP_E, vh), z = vfield((char*)a.scaled32 + r32, F::SP_E, vh);
+      const Field v32 = vfield((char*)a.out32 + r32, F::SP_E, vh), z32 = vfield((char*)a.scaled32 + r32, F::SP_E, vh);
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
         const cpx<float> v = {(float)o[c].r, (float)o[c].i};
-        F::put(y, 3 * w + c, off, v);
-        F::put(z, 3 * w + c, off, {v.r * a.scale, v.i * a.scale});
+        F::put(v32, 3 * w + c, off, v);
+        F::put(z32, 3 * w + c, off, {v.r * a.scale, v.i * a.scale});
         store_fence();
       }
       return;
@@ -324,7 +354,7 @@ hop_split_kernel(SplitArgs a) {
   const Field out = vec(a.out);
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    P::put(out, 3 * w + c, off, o[c]);
+    P::put(out, 3 * w + c, off, y[c]);
     store_fence();
   }
 }

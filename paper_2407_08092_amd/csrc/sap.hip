@@ -526,11 +526,7 @@ __device__ __forceinline__ void sap_lds_loads(const Geo& g, const int lc[4], int
 template <int H, bool L18, typename R>
 __device__ __forceinline__ void sap_lds_hop(Spinor<R>& acc, const Spinor<R>& nb, Link<R> u,
                                             const HopCtx<R>& c) {
-  if constexpr (!L18) {  // row 2 = conj(row 0 x row 1)
-    u.u[6] = conj(u.u[1] * u.u[5] - u.u[2] * u.u[4]);
-    u.u[7] = conj(u.u[2] * u.u[3] - u.u[0] * u.u[5]);
-    u.u[8] = conj(u.u[0] * u.u[4] - u.u[1] * u.u[3]);
-  }
+  if constexpr (!L18) su3_third_row(u);
   if constexpr (H & 1) {
     Link<R> d;
 #pragma unroll
