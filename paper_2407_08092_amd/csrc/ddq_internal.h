@@ -283,12 +283,12 @@ struct SapResidualSrc {
 // block Schur complement of D_kk e = r_k, then x += e on the block (FP64 full vectors r,
 // x); the block solve in FP64, or in FP32 (prec_f32) with FP32 links (12-real: link12)
 // and clover, all in SAP order (launch_sap_reorder).  res: the block solves form r
-// themselves from these sources (only where sap_on_chip holds); null: r is read
+// themselves from these sources (only where sap_fuses_residual holds); null: r is read
 hipError_t launch_sap_blocks(const Geo& g, int prec_f32, int link12, const d2_t* r, d2_t* x, const void* links_e,
                              const void* links_o, const void* clov_e, const void* clov_oi, int colour, int m,
                              const SapResidualSrc* res, hipStream_t s);
-// whether launch_sap_blocks solves this lattice's blocks on chip (and can form r itself)
-bool sap_on_chip(const Geo& g, int prec_f32, int link12);
+// whether launch_sap_blocks may form r itself: blocks solved on chip, none of a colour neighbours
+bool sap_fuses_residual(const Geo& g, int prec_f32, int link12);
 // r = b - D x (FP64 full vectors) at the sites of every 4^4 block of `colour`
 hipError_t launch_sap_residual(const Geo& g, const SapResidualSrc& src, d2_t* r, int colour, hipStream_t s);
 // copy of a blocked field of parity `parity` (erows element rows) into SAP order (the

@@ -292,7 +292,7 @@ __global__ void __launch_bounds__(SAP_HALF) k_sap_block(SapArgs a) {
 // FP32 blocks 532 -> 507 us, 32^3 x 64 1563 -> 1413, 8^4 119 -> 108; FP64 830 -> 789.  What
 // is left past L2, 1.24 GB a launch at 24^3 x 48, takes 200 us at 6.2 TB/s.  The
 // on-chip block solves form it in their prologue; k_sap_residual writes it out for the
-// other block-solve kernel.
+// other block-solve kernel and where blocks of one colour are neighbours (sap_fuses_residual).
 // ---------------------------------------------------------------------------
 // The block's sites of a full vector are 64 runs of 48 elements (4 sites x 12 rows, 16
 // bytes each).  In LDS: element row k of the site (parity q, half index j) at
@@ -880,8 +880,19 @@ hipError_t launch_sap_reorder(const Geo& g, int parity, const void* src, void* d
   return hipGetLastError();
 }
 
-bool sap_on_chip(const Geo& g, int prec_f32, int link12) {
+static bool sap_on_chip(const Geo& g, int prec_f32, int link12) {
   return (prec_f32 && link12) || (g.L[1] > SAP_B && g.L[2] > SAP_B && g.L[3] > SAP_B);
+}
+
+// With an odd number of blocks (three or more) along a direction the blocks on either side of the
+// boundary share a colour: one's prologue would read x where the other, in the same launch, writes
+// it.  A block that spans its direction is its own neighbour and reads before it writes.
+bool sap_fuses_residual(const Geo& g, int prec_f32, int link12) {
+  for (int mu = 0; mu < 4; ++mu) {
+    const int n = g.L[mu] / SAP_B;
+    if (n > 1 && n % 2 != 0) return false;
+  }
+  return sap_on_chip(g, prec_f32, link12);
 }
 
 template <typename R, bool L18>
@@ -900,7 +911,7 @@ hipError_t launch_sap_blocks(const Geo& g, int prec_f32, int link12, const d2_t*
   a.r = r;
   a.x = x;
   if (res) {
-    if (!sap_on_chip(g, prec_f32, link12)) return hipErrorInvalidValue;
+    if (!sap_fuses_residual(g, prec_f32, link12)) return hipErrorInvalidValue;
     a.res = *res;
   } else {
     a.res = SapResidualSrc{};

@@ -160,3 +160,47 @@ def test_fgmres_with_sap_matches_oracle(sap_n, sap_m, prec):
     assert rel(xh, res.x) < 1e-8
     with pytest.raises(api.DDQError):
         api.fgmres_sap_solve(c.lat, torch.from_numpy(b).cuda(), m=8, sap_n=1, sap_m=-1)
+
+
+@pytest.mark.parametrize("prec, link12, tol", [(api.DDQ_F64, False, 1e-12), (api.DDQ_F32, False, 1e-5), (api.DDQ_F32, True, 1e-5)])
+def test_sap_neighbours_of_one_colour(prec, link12, tol):
+    """Five, three or nine blocks along a direction and more blocks of a colour (562) than run at
+    once: a colour's residual is that of x before the colour, also where the blocks on either side
+    of the boundary share it, whichever of them comes first.  The reference takes every colour's
+    residual from the full operator and its block solves one colour at a time, with a right-hand
+    side that is zero elsewhere; the rounding tolerances are those of the oracle tests."""
+    dims = (20, 12, 20, 60)
+    lat = api.create_lattice(dims)
+    api.set_gauge(lat, synth.gauge_field(dims, 0.4, 521, device="cuda"), link12=link12)
+    api.set_clover(lat, 1.0, -0.2)
+    gen = torch.Generator(device="cuda").manual_seed(522)
+    b, x0 = (torch.view_as_complex(torch.randn(lat.full_shape + (2,), generator=gen, dtype=torch.float64, device="cuda"))
+             for _ in range(2))
+    lt, lz, ly, lx = lat.full_shape[:4]
+    at = [torch.arange(n, device="cuda") // 4 for n in (lt, lz, ly, lx)]
+    colour = ((at[0].view(-1, 1, 1, 1) + at[1].view(-1, 1, 1) + at[2].view(-1, 1) + at[3]) & 1)[..., None, None]
+    ref = x0.clone()
+    for _ in range(2):
+        for c in (0, 1):
+            r = torch.where(colour == c, b - api.apply_dirac(lat, ref), torch.zeros_like(b))
+            e = api.sap_smooth(lat, r, torch.zeros_like(b), 1, 3, prec=prec)
+            ref += torch.where(colour == c, e, torch.zeros_like(e))
+    got = [api.sap_smooth(lat, b, x0.clone(), 2, 3, prec=prec) for _ in range(2)]
+    assert torch.equal(got[0], got[1])
+    assert ((got[0] - ref).norm() / ref.norm()).item() < tol
+    api.destroy_lattice(lat)
+
+
+@pytest.mark.parametrize("dims, fused", [((12, 8, 8, 8), False), ((8, 8, 20, 8), False), ((8, 8, 8, 8), True), ((4, 8, 8, 8), True)],
+                         ids=lambda d: "x".join(map(str, d)) if isinstance(d, tuple) else str(d))
+def test_sap_fuses_only_where_colours_are_apart(dims, fused):
+    lat = api.create_lattice(dims)
+    api.set_gauge(lat, synth.gauge_field(dims, 0.4, 523, device="cuda"))
+    api.set_clover(lat, 1.0, -0.2)
+    b = torch.ones(lat.full_shape, dtype=torch.complex128, device="cuda")
+    for prec in (api.DDQ_F64, api.DDQ_F32):
+        api.profile_begin(lat)
+        api.sap_smooth(lat, b, torch.zeros_like(b), 1, 1, prec=prec)
+        kinds = " ".join(api.profile_end(lat))
+        assert ("sap_res_block" in kinds) == fused and ("sap_residual" in kinds) != fused
+    api.destroy_lattice(lat)
