@@ -660,6 +660,18 @@ int reconstruct_impl(ddq_lattice* L, int nrhs, const d2_t* x_e, const d2_t* b, d
   return DDQ_OK;
 }
 
+// whether kernels on `device` may read p in 16-byte elements: device memory of that GPU (another
+// GPU's may lie out of their reach, where a copy does not)
+bool kernels_may_load(const void* p, int device) {
+  hipPointerAttribute_t a{};
+  if (((uintptr_t)p & 15) != 0) return false;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == device;
+}
+
 }  // namespace
 
 // ===========================================================================
@@ -789,13 +801,14 @@ int ddq_set_gauge(ddq_lattice* L, const void* U, int U_on_device, unsigned stora
   L->have_clover = false;
   L->sap_prec = -1;
   L->sap_res_ok = false;
-  // the links are packed straight from the caller's device array; host links, and a device array
-  // off the 16-byte alignment of the loads, go through the lattice's own copy, which the first
-  // call takes with the other fields so that later ones allocate nothing
+  // the links are packed straight from the caller's array where it lies on the lattice's GPU; from
+  // elsewhere (host, managed and other GPUs' memory, also those the runtime says nothing about) they go through the
+  // lattice's own copy, which the first call takes with the other fields so that later ones
+  // allocate nothing
   const size_t ubytes = (size_t)L->V * 4 * 9 * 16;
   if (!L->U) CHK(dalloc(&L->U, ubytes));
   const d2_t* Ud = (const d2_t*)U;
-  if (!U_on_device || ((uintptr_t)U & 15)) {
+  if (!U_on_device || !kernels_may_load(U, L->device)) {
     HIPCHK(hipMemcpyAsync(L->U, U, ubytes, U_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, L->stream));
     Ud = (const d2_t*)L->U;
   }

@@ -1,0 +1,84 @@
+"""Which launches and copies a call makes, and with which arguments, without a GPU: the library runs
+in a process of its own on a stand-in for the HIP runtime (fake_hip.cpp) that executes nothing."""
+import ctypes as C
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+DEVICE, HOST, UNREGISTERED, MANAGED = 2, 1, 0, 3  # hipMemoryType
+KEEP = []
+
+
+class Event(C.Structure):
+    _fields_ = [("kind", C.c_int), ("name", C.c_char_p), ("ptr", C.c_void_p), ("grid", C.c_uint64), ("block", C.c_uint64)]
+
+
+def events(fake):
+    n = C.c_int()
+    e = fake.fake_events(C.byref(n))
+    return [dict(kind=e[k].kind, name=e[k].name.decode(), ptr=e[k].ptr, grid=e[k].grid, block=e[k].block) for k in range(n.value)]
+
+
+def lattice(L, dims):
+    h = C.c_void_p()
+    assert L.ddq_create_lattice((C.c_int * 4)(*dims), 1, None, C.byref(h)) == 0, L.ddq_last_error()
+    return h
+
+
+def gauge_source(fake, L, error, type_, device, ptr, on_device):
+    """ddq_set_gauge with links of these pointer attributes: its copies and launches."""
+    h = lattice(L, (4, 4, 4, 4))
+    fake.fake_pointer(error, type_, device)
+    events(fake)
+    assert L.ddq_set_gauge(h, C.c_void_p(ptr), on_device, 1) == 0, L.ddq_last_error()
+    return events(fake)
+
+
+def main(fake_path, call, args):
+    fake = C.CDLL(fake_path, mode=C.RTLD_GLOBAL)
+    fake.fake_events.restype = C.POINTER(Event)
+    sys.path.insert(0, os.path.dirname(HERE))
+    from paper_2407_08092_amd import _lib
+
+    print(json.dumps(globals()[call](fake, _lib.lib(), *args)))
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", os.path.join(HERE, "fake_hip.cpp"), "-o", so, "-ldl"], check=True)
+
+    def go(call, *args):
+        r = subprocess.run([sys.executable, __file__, so, call, json.dumps(args)], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stdout + r.stderr
+        return json.loads(r.stdout.splitlines()[-1])
+
+    return go
+
+
+U = 0x7F0000000000
+
+
+@pytest.mark.parametrize("error, type_, device, ptr, in_place", [
+    (0, DEVICE, 0, U, True),
+    (0, DEVICE, 0, U + 8, False),      # off the loads' alignment
+    (0, DEVICE, 1, U, False),          # another GPU's memory: a copy works where a kernel's load may not
+    (0, HOST, 0, U, False),
+    (0, MANAGED, 0, U, False),
+    (0, UNREGISTERED, 0, U, False),
+    (1, DEVICE, 0, U, False),          # an address the runtime does not know
+])
+def test_links_are_read_in_place_only_from_the_lattices_gpu(run, error, type_, device, ptr, in_place):
+    ev = run("gauge_source", error, type_, device, ptr, 1)
+    pack = [e for e in ev if "k_pack_gauge" in e["name"]]
+    assert len(pack) == 1
+    assert (pack[0]["ptr"] == ptr) == in_place
+    assert [e["ptr"] for e in ev if e["kind"] == 0] == ([] if in_place else [ptr])
+
+
+if __name__ == "__main__":
+    main(sys.argv[1], sys.argv[2], json.loads(sys.argv[3]))
