@@ -359,17 +359,24 @@ hop_split_kernel(SplitArgs a) {
   }
 }
 
+// slab order; with fewer groups of 64 sites a slice it leaves XCDs without work
+static bool split_slab(const Geo& g) { return (g.sT + 63) / 64 >= 8; }
+// workgroups of a launch on t_cnt slices
+static long long split_grid(const Geo& g, int t_cnt, int nrhs) {
+  const int ng = (g.sT + 63) / 64;
+  return split_slab(g) ? 8LL * t_cnt * ((ng + 7) / 8) * nrhs : ((long long)t_cnt * g.sT + 63) / 64 * nrhs;
+}
+constexpr long long SPLIT_MAX_GRID = 0xffffffffLL / 256;  // a launch has fewer than 2^32 threads
+
 template <class P>
 static hipError_t split_launch(SplitArgs a, int mode, hipStream_t s) {
-  const int ng = (a.g.sT + 63) / 64;
   if (a.t_cnt <= 0) {
     a.t_lo = 0;
     a.t_cnt = a.g.L[3];
   }
-  a.slab = ng >= 8;  // with fewer groups a slice, slab order leaves XCDs without work
-  const long long grid = a.slab ? 8LL * a.t_cnt * ((ng + 7) / 8) * a.nrhs
-                                : ((long long)a.t_cnt * a.g.sT + 63) / 64 * a.nrhs;
-  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  a.slab = split_slab(a.g);
+  const long long grid = split_grid(a.g, a.t_cnt, a.nrhs);
+  if (grid > SPLIT_MAX_GRID) return hipErrorInvalidValue;
   const dim3 g((unsigned)grid), b(256);
   constexpr bool WIDE = sizeof(typename P::R) == 8;  // the modes of eq. 2 and the residual run in FP64 only
   switch (mode) {
@@ -400,8 +407,10 @@ static hipError_t split_launch(SplitArgs a, int mode, hipStream_t s) {
 //     40^3 x 64 3220 -> 2919, 5 on 32^3 x 64 4466 -> 3120;
 //   16 bits: 65,536 sites (16^3 x 32 20 -> 17), 20^3 x 32 (128,000) 25 -> 28; three right-hand
 //     sides 16^4 15 -> 11, 16^3 x 32 16 -> 19 (the one-thread kernel shares a link among three).
+// And four threads a site reach a launch's limit of threads at a quarter of the sites.
 bool hop_split_takes(const Geo& g, int bytes_per_complex, int nrhs) {
   const long long n = (long long)g.Vh * nrhs;
+  if (split_grid(g, g.L[3], nrhs) > SPLIT_MAX_GRID) return false;
   if (bytes_per_complex == 4) return n <= (nrhs == 1 ? 65536 : 98304);
   if (bytes_per_complex == 8) return nrhs > 1 || n <= 400000;
   return nrhs > 1 || n <= 40960;

@@ -10,7 +10,7 @@ import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 DEVICE, HOST, UNREGISTERED, MANAGED = 2, 1, 0, 3  # hipMemoryType
-KEEP = []
+U = 0x7F0000000000
 
 
 class Event(C.Structure):
@@ -38,6 +38,18 @@ def gauge_source(fake, L, error, type_, device, ptr, on_device):
     return events(fake)
 
 
+def applies(fake, L, dims, nrhs, prec):
+    """The stencil launches of one apply on nrhs right-hand sides."""
+    h = lattice(L, dims)
+    fake.fake_pointer(0, DEVICE, 0)
+    assert L.ddq_set_gauge(h, C.c_void_p(U), 1, 1 | 2) == 0, L.ddq_last_error()
+    assert L.ddq_set_clover(h, 1.0, 0.1) == 0, L.ddq_last_error()
+    assert L.ddq_reserve(h, nrhs, 0, 0) == 0, L.ddq_last_error()
+    events(fake)
+    assert L.ddq_apply_schur(h, prec, nrhs, C.c_void_p(U), C.c_void_p(2 * U), 0) == 0, L.ddq_last_error()
+    return [e for e in events(fake) if e["kind"] == 1]
+
+
 def main(fake_path, call, args):
     fake = C.CDLL(fake_path, mode=C.RTLD_GLOBAL)
     fake.fake_events.restype = C.POINTER(Event)
@@ -60,9 +72,6 @@ def run(tmp_path_factory):
     return go
 
 
-U = 0x7F0000000000
-
-
 @pytest.mark.parametrize("error, type_, device, ptr, in_place", [
     (0, DEVICE, 0, U, True),
     (0, DEVICE, 0, U + 8, False),      # off the loads' alignment
@@ -78,6 +87,17 @@ def test_links_are_read_in_place_only_from_the_lattices_gpu(run, error, type_, d
     assert len(pack) == 1
     assert (pack[0]["ptr"] == ptr) == in_place
     assert [e["ptr"] for e in ev if e["kind"] == 0] == ([] if in_place else [ptr])
+
+
+# 2 x 2 x 258 x 256: the slab order's padding doubles the workgroups (4096 right-hand sides: 52 GB
+# a vector in FP32)
+@pytest.mark.parametrize("dims, nrhs, split", [((48, 48, 48, 96), 2, True), ((2, 2, 258, 256), 2, True), ((2, 2, 258, 256), 4096, False)])
+def test_a_launch_stays_below_the_limit_of_threads(run, dims, nrhs, split):
+    ev = run("applies", list(dims), nrhs, 1)
+    assert len(ev) == 2
+    for e in ev:
+        assert e["grid"] * e["block"] < 2**32
+        assert ("hop_split_kernel" in e["name"]) == split
 
 
 if __name__ == "__main__":
