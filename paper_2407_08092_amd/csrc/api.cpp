@@ -288,7 +288,7 @@ hipError_t launch_any(ddq_lattice* L, const HopArgs<R>& a, int mode, bool dag, i
       return launch_hop_rb(b, mode, nrhs, L->stream);
     }
   }
-  if (mode == M_PREP || mode == M_RECON || (!t && hop_split_takes(L->geo, sizeof(pair<R>), nrhs)))
+  if (mode == M_PREP || mode == M_RECON || (!t && hop_split_takes(L->geo, sizeof(pair<R>), nrhs, a.sweep)))
     return launch_hop_split<R>(a, mode, dag, nrhs, L->stream);
   // one right-hand side per thread: the workgroup order of an nb = 0 tile set for
   // nrhs, else slab order
@@ -376,7 +376,7 @@ hipError_t run_hop16(ddq_lattice* L, int prec, int nrhs, int mode, const void* i
   const MrTile* t = nrhs > 1 ? L->tile_for(nrhs) : nullptr;
   a.chunk = t ? t->xmap : XMAP_SLAB;
   auto launch = [&]() {
-    return !t && hop_split_takes(L->geo, 4, nrhs) ? launch_hop16_split(h16_kind(prec), a, mode, L->stream)
+    return !t && hop_split_takes(L->geo, 4, nrhs, sweep) ? launch_hop16_split(h16_kind(prec), a, mode, L->stream)
                                                   : launch_hop16(h16_kind(prec), a, mode, L->stream);
   };
   if (!L->prof_on || g_no_alloc_call) return launch();
@@ -500,6 +500,7 @@ int sweep_chunked(ddq_lattice* L, int prec, const pair<R>* x, const pair<R>* b, 
     HopArgs<R> a = hop_args<R>(L, prec, 1);
     a.in = x;
     a.out = u;
+    a.sweep = mode == M_RICH;
     a.t_lo = lo(c);
     a.t_cnt = lo(c + 1) - lo(c);
     return run_hop<R>(L, a, M_HOP_CLINV, dag, 1);
@@ -511,6 +512,7 @@ int sweep_chunked(ddq_lattice* L, int prec, const pair<R>* x, const pair<R>* b, 
     a.b = b;
     a.out = out;
     a.omega = omega;
+    a.sweep = mode == M_RICH;
     a.t_lo = lo(c);
     a.t_cnt = lo(c + 1) - lo(c);
     return run_hop<R>(L, a, mode, dag, 1);

@@ -35,13 +35,15 @@ __device__ __forceinline__ void third_row_as_hop(Link<R>& l) {
   l.u[8] = {re(u[0], u[4]) - re(u[1], u[3]), -(im0(u[4]) - im(u[1], u[3]))};
 }
 
-// Storage policies: how a precision's fields are read and written.  KEEP: the operator's
-// fields fit the Infinity Cache and everything may stay there; else links and results are
-// streamed past it.
-template <typename RR, bool L12, bool KEEP>
+// What a launch streams past the Infinity Cache (split_policy); everything else may stay there.
+enum SplitStream { ST_NONE = 0, ST_LINKS = 1, ST_LINKS_RESULT = 2 };
+
+// Storage policies: how a precision's fields are read and written.  NT: a SplitStream
+template <typename RR, bool L12, int NT>
 struct SplitR {
   using R = RR;
-  static constexpr int LINK_AUX = KEEP ? 0 : DDQ_STREAM_AUX, ST_AUX = KEEP ? 0 : DDQ_STORE_AUX;
+  static constexpr int STREAM = NT;
+  static constexpr int LINK_AUX = NT >= ST_LINKS ? DDQ_STREAM_AUX : 0, ST_AUX = NT == ST_LINKS_RESULT ? DDQ_STORE_AUX : 0;
   static constexpr int SP_E = SPINOR_ROWS / CPE<R>, CL_E = CLOVER_ROWS / CPE<R>;
   static constexpr int LK_E = (L12 ? LINK12_ROWS : LINK_ROWS) / CPE<R>;
   static __device__ __forceinline__ Spinor<R> spinor(const Field& v, uint32_t off) { return load_spinor<R>(v, off); }
@@ -86,15 +88,17 @@ struct SplitR {
   }
 };
 
-template <typename S, bool C32>
+template <typename S, bool C32, int NT>
 struct Split16 {
   using R = float;
+  static constexpr int STREAM = NT;
+  static constexpr int LINK_AUX = NT >= ST_LINKS ? DDQ_STREAM_AUX : 0;
   static constexpr int SP_E = SP16_E, LK_E = LK16_E, CL_E = C32 ? CLOVER_ROWS / CPE<float> : CL16_E;
   static __device__ __forceinline__ Spinor<R> spinor(const Field& v, uint32_t off) { return load_spinor16<S>(v, off); }
   static __device__ __forceinline__ void links(const Field& U, uint32_t off, Link<R>& f, Link<R>& b) {
     cpx<R> l[12];
 #pragma unroll
-    for (int e = 0; e < LK16_E; ++e) unpack4<S>(ld16(U, e, off), l + 4 * e);
+    for (int e = 0; e < LK16_E; ++e) unpack4<S>(ld16<LINK_AUX>(U, e, off), l + 4 * e);
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
       f.u[k] = l[k];
@@ -195,6 +199,7 @@ struct SplitArgs {
   double omega;
   int nrhs;
   int dagger;
+  int sweep;        // part of a Richardson sweep (split_policy)
   int slab;         // slab order; else the groups of 64 sites in a row
   int t_lo, t_cnt;  // output sites of slices [t_lo, t_lo + t_cnt)
   // M_PREP, M_RECON: b is a full FP64 vector
@@ -338,7 +343,7 @@ hop_split_kernel(SplitArgs a) {
   if (!ok) return;
   if constexpr (MODE == M_PREP) {
     if (a.out32) {  // uniform
-      using F = SplitR<float, false, true>;
+      using F = SplitR<float, false, ST_NONE>;
       const size_t r32 = (size_t)rhs * F::SP_E * (size_t)vh * 16;
       const Field v32 = vfield((char*)a.out32 + r32, F::SP_E, vh), z32 = vfield((char*)a.scaled32 + r32, F::SP_E, vh);
 #pragma unroll
@@ -359,12 +364,18 @@ hop_split_kernel(SplitArgs a) {
   }
 }
 
-// slab order; with fewer groups of 64 sites a slice it leaves XCDs without work
-static bool split_slab(const Geo& g) { return (g.sT + 63) / 64 >= 8; }
+// Slab order, but with fewer than eight groups of 64 sites a slice it leaves XCDs without work, and
+// where an XCD's last group is missing on most of them (9 to 11 groups, or 17) one right-hand side
+// waits for the others: 12 x 12 x 8 x 64 FP32 26 us an apply against 21 with the groups in a row.
+// Several right-hand sides share the links that the order keeps together (5: 63 against 71).
+static bool split_slab(const Geo& g, int nrhs) {
+  const int ng = (g.sT + 63) / 64, padded = (ng + 7) / 8 * 8;
+  return ng >= 8 && (nrhs > 1 || 5 * padded <= 7 * ng);
+}
 // workgroups of a launch on t_cnt slices
 static long long split_grid(const Geo& g, int t_cnt, int nrhs) {
   const int ng = (g.sT + 63) / 64;
-  return split_slab(g) ? 8LL * t_cnt * ((ng + 7) / 8) * nrhs : ((long long)t_cnt * g.sT + 63) / 64 * nrhs;
+  return split_slab(g, nrhs) ? 8LL * t_cnt * ((ng + 7) / 8) * nrhs : ((long long)t_cnt * g.sT + 63) / 64 * nrhs;
 }
 constexpr long long SPLIT_MAX_GRID = 0xffffffffLL / 256;  // a launch has fewer than 2^32 threads
 
@@ -374,53 +385,90 @@ static hipError_t split_launch(SplitArgs a, int mode, hipStream_t s) {
     a.t_lo = 0;
     a.t_cnt = a.g.L[3];
   }
-  a.slab = split_slab(a.g);
+  a.slab = split_slab(a.g, a.nrhs);
   const long long grid = split_grid(a.g, a.t_cnt, a.nrhs);
   if (grid > SPLIT_MAX_GRID) return hipErrorInvalidValue;
   const dim3 g((unsigned)grid), b(256);
-  constexpr bool WIDE = sizeof(typename P::R) == 8;  // the modes of eq. 2 and the residual run in FP64 only
+#define DDQ_SPLIT_LAUNCH(M, TAKEN)                                            \
+  case M:                                                                     \
+    if constexpr (!(TAKEN)) return hipErrorInvalidValue;                      \
+    else hipLaunchKernelGGL((hop_split_kernel<P, M>), g, b, 0, s, a);         \
+    break
+  // the modes of eq. 2 and the residual run in FP64 only; applies and sweeps as split_policy has them
+  constexpr bool WIDE = sizeof(typename P::R) == 8;
   switch (mode) {
-    case M_HOP_CLINV: hipLaunchKernelGGL((hop_split_kernel<P, M_HOP_CLINV>), g, b, 0, s, a); break;
-    case M_APPLY: hipLaunchKernelGGL((hop_split_kernel<P, M_APPLY>), g, b, 0, s, a); break;
-    case M_RICH: hipLaunchKernelGGL((hop_split_kernel<P, M_RICH>), g, b, 0, s, a); break;
-    case M_RECON: if constexpr (WIDE) { hipLaunchKernelGGL((hop_split_kernel<P, M_RECON>), g, b, 0, s, a); break; }
-    case M_RESID: if constexpr (WIDE) { hipLaunchKernelGGL((hop_split_kernel<P, M_RESID>), g, b, 0, s, a); break; }
-    case M_PREP: if constexpr (WIDE) { hipLaunchKernelGGL((hop_split_kernel<P, M_PREP>), g, b, 0, s, a); break; }
+    DDQ_SPLIT_LAUNCH(M_HOP_CLINV, true);
+    DDQ_SPLIT_LAUNCH(M_APPLY, P::STREAM != ST_LINKS_RESULT);
+    DDQ_SPLIT_LAUNCH(M_RICH, P::STREAM != ST_LINKS);
+    DDQ_SPLIT_LAUNCH(M_RECON, WIDE);
+    DDQ_SPLIT_LAUNCH(M_RESID, WIDE);
+    DDQ_SPLIT_LAUNCH(M_PREP, WIDE);
     default: return hipErrorInvalidValue;
   }
+#undef DDQ_SPLIT_LAUNCH
   return hipGetLastError();
 }
 
-// Where four threads a site beat one (microseconds a sweep, one thread -> four):
-//   FP64, one right-hand side: latency-bound launches only; 8^4 31 -> 11, 16^4 42 -> 30.
-//     Repeated sweeps gain up to 200,000 sites (20^3 x 32 114 -> 95), but a lone apply that
-//     finds its fields in no cache does not (28^3 x 16 145 -> 152; applies after set_gauge
-//     and set_clover on 16^3 x 32 cost 10 more), and above that repeated ones depend on the
-//     shape (28^3 x 24 230 -> 217, 28^3 x 32 289 -> 316);
-//   FP32, one: up to 400,000 sites; 8^4 19 -> 9, 16^3 x 32 31 -> 27, 24^3 x 48 (331,776) 142 -> 124,
-//     while 32^4 (524,288) 203 -> 205 (a t-slice's share per XCD has outgrown the sites in flight,
-//     so fewer of them no longer help L2); with the fields in no cache 16^3 x 32 36 -> 35,
-//     24^3 x 32 103 -> 103, 24^3 x 48 150 -> 144;
+// Where four threads a site beat one.  Microseconds, one thread a site -> four, with the fields as
+// left by the same call before / x written by another kernel just before / 1 GB written just
+// before / 1 GB read just before:
+//   FP64, one right-hand side: 8^4 20 -> 12 / 20 -> 12 / 34 -> 15 / 34 -> 15, 20 x 16^3 (40,960 sites)
+//     44 -> 38 / 46 -> 38 / 48 -> 48 / 45 -> 41.  Repeated sweeps gain up to 200,000 sites, but a lone
+//     apply that finds its fields in no cache does not (16^3 x 32 55 -> 53 / 57 -> 53 / 59 -> 67 / 56 -> 57);
+//   FP32, one: applies up to 40,960 sites (26 -> 23 / 27 -> 24 / 28 -> 28 / 27 -> 25), again from 65,536
+//     sites, where one thread a site begins a second wavefront on a SIMD (65,536: 30 -> 31 / 32 -> 31 /
+//     33 -> 38 / 32 -> 33; 82,944: 46 -> 38 / 48 -> 39 / 49 -> 49 / 47 -> 43), to 340,000 (24^3 x 48
+//     139 -> 125 / 142 -> 133 / 150 -> 148 / 139 -> 135; 28^3 x 32 143 -> 143 / 149 -> 147 / 158 -> 157 /
+//     144 -> 148); between them 1 GB written just before costs up to 8 % (24^2 x 20 x 32 78 -> 69 / 79 ->
+//     70 / 84 -> 91 / 78 -> 80).  Sweeps to 400,000 sites: two on 16^3 x 32 63 -> 57, on 24^3 x 48 287 -> 250,
+//     on 387,072 sites 308 -> 303;
 //   several: the wavefronts of one 64-site group follow each other and take links and clover
-//     from L2; FP32 (no tile set) at every size measured, 2 right-hand sides on 32^3 x 64 889 ->
-//     723, 5 on 24^3 x 48 700 -> 487; FP64 too, 2 on 24^3 x 48 498 -> 469, on 32^4 760 -> 752 and on
-//     40^3 x 64 3220 -> 2919, 5 on 32^3 x 64 4466 -> 3120;
-//   16 bits: 65,536 sites (16^3 x 32 20 -> 17), 20^3 x 32 (128,000) 25 -> 28; three right-hand
-//     sides 16^4 15 -> 11, 16^3 x 32 16 -> 19 (the one-thread kernel shares a link among three).
+//     from L2, at every size measured.  FP32 (no tile set): 2 on 16^3 x 32 51 -> 36 / 52 -> 36 / 55 -> 60 /
+//     51 -> 45, 4 on 32^4 571 -> 575 (the closest: the one-thread kernel takes four together) and on
+//     32^3 x 64 1176 -> 1122, 12 on 40^3 x 48 5054 -> 4555; FP64: 2 on 16^3 x 32 108 -> 79 / 107 -> 80 /
+//     113 -> 103 / 108 -> 82, 8 on 32^3 x 64 4720 -> 4154;
+//   16 bits, one: 65,536 sites (20 -> 20 / 21 -> 21 / 22 -> 23 / 22 -> 21), 73,728 26 -> 28, 128,000 28 -> 29.
+//     Several, against a kernel that shares a link among two or three: 2 on 49,152 sites 26 -> 23,
+//     3 on 32,768 31 -> 23, 9 on 10,368 30 -> 26, 16 on 4,096 24 -> 17 and on 4,608 24 -> 27; counts that
+//     two and three do not divide, where it shares nothing and has the more wavefronts: 5 on 4,608
+//     15 -> 14 and on 10,368 16 -> 18, 7 on 4,096 17 -> 13 and on 4,608 15 -> 17.
 // And four threads a site reach a launch's limit of threads at a quarter of the sites.
-bool hop_split_takes(const Geo& g, int bytes_per_complex, int nrhs) {
+bool hop_split_takes(const Geo& g, int bytes_per_complex, int nrhs, bool sweep) {
   const long long n = (long long)g.Vh * nrhs;
   if (split_grid(g, g.L[3], nrhs) > SPLIT_MAX_GRID) return false;
-  if (bytes_per_complex == 4) return n <= (nrhs == 1 ? 65536 : 98304);
-  if (bytes_per_complex == 8) return nrhs > 1 || n <= 400000;
-  return nrhs > 1 || n <= 40960;
+  if (bytes_per_complex == 4)
+    return n <= (nrhs == 1 || nrhs > 9 ? 65536 : nrhs % 2 != 0 && nrhs % 3 != 0 ? 24576 : 98304);
+  if (nrhs > 1) return true;
+  if (bytes_per_complex == 16) return n <= 40960;
+  return sweep ? n <= 400000 : n <= 40960 || (n > 65536 && n <= 340000);
+}
+
+// What a launch streams past the Infinity Cache.  A line that is allocated there pushes another one
+// out, which has to be written back first where an earlier kernel wrote it.
+// * One right-hand side, a lone launch: the links, read once and the largest part.  FP32 applies as
+//   above, nothing streamed -> links: 16^4 18 -> 19 / 19 -> 20 / 29 -> 23 / 21 -> 20, 24^3 x 32 95 -> 79 /
+//   97 -> 79 / 127 -> 105 / 98 -> 96; FP16 16^3 x 32 19 -> 20 / 20 -> 21 / 26 -> 23 / 21 -> 21.  The results
+//   too: 24^3 x 32 84 / 84 / 116 / 99; clover blocks, which two wavefronts read, too: 16^3 x 32 31 -> 35.
+// * One right-hand side in a sweep, whose next launches read the same fields: nothing where the
+//   links and clover blocks of both parities fit the cache's 256 MB, else links and results (24^3 x 48
+//   six FP32 sweeps 739, links only 778, nothing 852).
+// * Several: nothing; the next wavefronts read the links again (streamed with the results: 2 on 32^4
+//   FP32 329 -> 342, 4 575 -> 617, 8 on 32^3 x 64 FP64 4154 -> 4474).
+static int split_policy(const SplitArgs& a, long long field_bytes) {
+  if (a.nrhs > 1) return ST_NONE;
+  if (!a.sweep) return ST_LINKS;
+  return field_bytes <= (256LL << 20) ? ST_NONE : ST_LINKS_RESULT;
 }
 
 template <typename R, bool L12>
 static hipError_t split_launch_r(const SplitArgs& a, int mode, hipStream_t s) {
-  // links and clover blocks of both parities, against the 256 MB of the Infinity Cache
-  const long long fields = 2LL * a.g.Vh * ((L12 ? 4 * LINK12_ROWS : 4 * LINK_ROWS) + CLOVER_ROWS) * (long long)sizeof(pair<R>);
-  return fields <= (256LL << 20) ? split_launch<SplitR<R, L12, true>>(a, mode, s) : split_launch<SplitR<R, L12, false>>(a, mode, s);
+  switch (split_policy(a, 2LL * a.g.Vh * ((L12 ? 4 * LINK12_ROWS : 4 * LINK_ROWS) + CLOVER_ROWS) * (long long)sizeof(pair<R>))) {
+    case ST_NONE: return split_launch<SplitR<R, L12, ST_NONE>>(a, mode, s);
+    case ST_LINKS: return split_launch<SplitR<R, L12, ST_LINKS>>(a, mode, s);
+  }
+  // in FP64 hop_split_takes has no sweep of one right-hand side past the cache
+  if constexpr (sizeof(R) == 4) return split_launch<SplitR<R, L12, ST_LINKS_RESULT>>(a, mode, s);
+  return split_launch<SplitR<R, L12, ST_NONE>>(a, mode, s);
 }
 
 template <typename R>
@@ -437,6 +485,7 @@ hipError_t launch_hop_split(const HopArgs<R>& h, int mode, bool dagger, int nrhs
   a.omega = (double)h.omega;
   a.nrhs = nrhs;
   a.dagger = dagger ? 1 : 0;
+  a.sweep = h.sweep;
   a.t_lo = h.t_lo;
   a.t_cnt = h.t_cnt;
   a.full = h.full;
@@ -451,6 +500,13 @@ hipError_t launch_hop_split(const HopArgs<R>& h, int mode, bool dagger, int nrhs
 template hipError_t launch_hop_split<double>(const HopArgs<double>&, int, bool, int, hipStream_t);
 template hipError_t launch_hop_split<float>(const HopArgs<float>&, int, bool, int, hipStream_t);
 
+template <typename S>
+static hipError_t split_launch_16(const SplitArgs& a, bool c32, int mode, hipStream_t s) {
+  if (split_policy(a, 0) == ST_LINKS)  // a field of the sizes that hop_split_takes fits the cache
+    return c32 ? split_launch<Split16<S, true, ST_LINKS>>(a, mode, s) : split_launch<Split16<S, false, ST_LINKS>>(a, mode, s);
+  return c32 ? split_launch<Split16<S, true, ST_NONE>>(a, mode, s) : split_launch<Split16<S, false, ST_NONE>>(a, mode, s);
+}
+
 hipError_t launch_hop16_split(int kind, const Hop16Args& h, int mode, hipStream_t s) {
   SplitArgs a{};
   a.g = h.g;
@@ -464,9 +520,8 @@ hipError_t launch_hop16_split(int kind, const Hop16Args& h, int mode, hipStream_
   a.omega = (double)h.omega;
   a.nrhs = h.nrhs;
   if (h.nrhs < 1) return hipErrorInvalidValue;
-  if (kind == H16_BF16)
-    return h.clov32 ? split_launch<Split16<__bf16, true>>(a, mode, s) : split_launch<Split16<__bf16, false>>(a, mode, s);
-  return h.clov32 ? split_launch<Split16<_Float16, true>>(a, mode, s) : split_launch<Split16<_Float16, false>>(a, mode, s);
+  a.sweep = h.sweep;
+  return kind == H16_BF16 ? split_launch_16<__bf16>(a, h.clov32 != nullptr, mode, s) : split_launch_16<_Float16>(a, h.clov32 != nullptr, mode, s);
 }
 
 }  // namespace ddq
