@@ -5,11 +5,6 @@
 
 namespace ddq {
 
-// lexicographic index of coordinates (x, y, z, t)
-__device__ __forceinline__ long long lex(const Geo& g, int x, int y, int z, int t) {
-  return x + (long long)g.L[0] * (y + (long long)g.L[1] * (z + (long long)g.L[2] * t));
-}
-
 // ---------------------------------------------------------------------------
 // gauge packing: per parity p, direction mu and site i, complex rows 0..8 = U_mu(x)
 // and rows 9..17 = U_mu(x-mu)^H (FP64: one complex per 16-byte element), and in the same

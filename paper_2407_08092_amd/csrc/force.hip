@@ -20,6 +20,7 @@
 // W~ is anti-Hermitian: nine real numbers, stored per parity and plane as INS_E element rows of
 // 64-site blocks like the packed links, which the link kernel reads in place of the canonical
 // ones, so that every load of a wavefront is a run of 16-byte elements.
+#include "full_rows.h"
 #include "gauge_common.h"
 
 namespace ddq {
@@ -271,9 +272,7 @@ k_force_links(Geo g, PackedLinks L, const d2_t* __restrict__ W, ParityPair av, P
     }
   }
   if (!G) return;  // uniform
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  wave_lds_order();
   // M^H of the wavefront's links, nine lanes a link
   for (int q = lane; q < (end - base) * 9; q += 64) {
     const int sl = q / 9, e = q - 9 * sl;

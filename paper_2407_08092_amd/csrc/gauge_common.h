@@ -35,20 +35,6 @@ __device__ __forceinline__ C3 c3_mul(const C3& A, const C3& B) {
     }
   return C;
 }
-// A^H B
-__device__ __forceinline__ C3 c3_dag_mul(const C3& A, const C3& B) {
-  C3 C;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      cpx<double> s = {0.0, 0.0};
-#pragma unroll
-      for (int k = 0; k < 3; ++k) cfma_conj(s, A.a[k][i], B.a[k][j]);
-      C.a[i][j] = s;
-    }
-  return C;
-}
 // X = X B (DAG: X B^H), row by row
 template <bool DAG>
 __device__ __forceinline__ void c3_rmul(C3& X, const C3& B) {
@@ -69,20 +55,6 @@ __device__ __forceinline__ void c3_rmul(C3& X, const C3& B) {
 #pragma unroll
     for (int j = 0; j < 3; ++j) X.a[i][j] = row[j];
   }
-}
-// A B^H
-__device__ __forceinline__ C3 c3_mul_dag(const C3& A, const C3& B) {
-  C3 C;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      cpx<double> s = {0.0, 0.0};
-#pragma unroll
-      for (int k = 0; k < 3; ++k) cfma_conj(s, B.a[j][k], A.a[i][k]);
-      C.a[i][j] = s;
-    }
-  return C;
 }
 __device__ __forceinline__ C3 c3_dag(const C3& A) {
   C3 C;

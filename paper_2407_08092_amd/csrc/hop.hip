@@ -276,14 +276,29 @@ static hipError_t launch_mode(const HopArgs<R>& a, bool dagger, int nrhs, hipStr
   } else {                                \
     DDQ_HOP_LAUNCH_D(false, M, CP);       \
   }
+  // a sweep's launches; in FP32 those that reach this kernel are past the sites whose clover blocks fit
+  if constexpr (MODE == M_HOP_CLINV || MODE == M_RICH) {
+    if (nrhs == 1 && !dagger) {
+      const int cp = cache_policy(a.sweep, a.g.Vh, SPINOR_ROWS * (int)sizeof(pair<R>), CLOVER_ROWS * (int)sizeof(pair<R>));
+      if constexpr (!F32) {
+        if (cp == CP_VECTORS_CLOVER) {
+          DDQ_HOP_LAUNCH(false, false, false, CP_VECTORS_CLOVER);
+          return hipGetLastError();
+        }
+      }
+      if (cp != CP_STREAM) {
+        if (l12)
+          DDQ_HOP_LAUNCH(false, F32, false, CP_VECTORS);
+        else
+          DDQ_HOP_LAUNCH(false, false, false, CP_VECTORS);
+        return hipGetLastError();
+      }
+    }
+  }
   if (nrhs > 1) {
     DDQ_HOP_LAUNCH_L(true, CP_STREAM)
   } else {
-    switch (cache_policy(a.sweep, a.g.Vh, SPINOR_ROWS * (int)sizeof(pair<R>), CLOVER_ROWS * (int)sizeof(pair<R>))) {
-      case CP_VECTORS_CLOVER: DDQ_HOP_LAUNCH_L(false, CP_VECTORS_CLOVER) break;
-      case CP_VECTORS: DDQ_HOP_LAUNCH_L(false, CP_VECTORS) break;
-      default: DDQ_HOP_LAUNCH_L(false, CP_STREAM) break;
-    }
+    DDQ_HOP_LAUNCH_L(false, CP_STREAM)
   }
 #undef DDQ_HOP_LAUNCH_L
 #undef DDQ_HOP_LAUNCH_D

@@ -188,7 +188,10 @@ template <typename S, int NB, bool C32, int CP>
 static hipError_t launch16_c(const Hop16Args& a, int mode, dim3 grid, dim3 block, hipStream_t s) {
   switch (mode) {
     case M_HOP_CLINV: hipLaunchKernelGGL((hop16_kernel<S, M_HOP_CLINV, NB, C32, CP>), grid, block, 0, s, a); break;
-    case M_APPLY: hipLaunchKernelGGL((hop16_kernel<S, M_APPLY, NB, C32, CP>), grid, block, 0, s, a); break;
+    case M_APPLY:  // no part of a sweep
+      if constexpr (CP != CP_STREAM) return hipErrorInvalidValue;
+      else hipLaunchKernelGGL((hop16_kernel<S, M_APPLY, NB, C32, CP>), grid, block, 0, s, a);
+      break;
     case M_RICH: hipLaunchKernelGGL((hop16_kernel<S, M_RICH, NB, C32, CP>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
@@ -203,7 +206,7 @@ static hipError_t launch16_nb(const Hop16Args& a, int mode, hipStream_t s) {
 #define DDQ_H16_LAUNCH(CP) \
   return a.clov32 ? launch16_c<S, NB, true, CP>(a, mode, grid, block, s) : launch16_c<S, NB, false, CP>(a, mode, grid, block, s)
   if constexpr (NB == 1) {
-    if (a.nrhs == 1) {
+    if (a.nrhs == 1 && mode != M_APPLY) {
       const int cp = cache_policy(a.sweep, a.g.Vh, SP16_E * 16, a.clov32 ? CLOVER_ROWS * 8 : CL16_E * 16);
       if (cp == CP_VECTORS_CLOVER) DDQ_H16_LAUNCH(CP_VECTORS_CLOVER);
       if (cp == CP_VECTORS) DDQ_H16_LAUNCH(CP_VECTORS);
