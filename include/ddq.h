@@ -124,16 +124,17 @@ int ddq_lattice_size(const ddq_lattice* lat, int64_t* volume, int64_t* half_volu
  *             vectors per right-hand side, 2 max_m + 2 full FP64 vectors);
  *             DDQ_RESERVE_SAP: ddq_sap_smooth / ddq_fgmres_sap_solve (SAP-ordered
  *             copies of links and clover, the residual work space, FGMRES);
- *             DDQ_RESERVE_FORCE: ddq_backward_link_force (V x 54 complex128
- *             insertions and two parity vectors)
+ *             DDQ_RESERVE_FORCE: ddq_backward_link_force (480 bytes of
+ *             insertions a site and two parity vectors)
  * Returns DDQ_ERR_OOM when the device memory does not suffice (the reservation then
  * keeps what it had). */
 enum { DDQ_RESERVE_SOLVE = 1, DDQ_RESERVE_FULL = 2, DDQ_RESERVE_SAP = 4, DDQ_RESERVE_FORCE = 8 };
 int ddq_reserve(ddq_lattice* lat, int max_nrhs, int max_m, unsigned what);
 
 /* Gauge links U (canonical layout, SU(3), complex128; host pointer when
- * U_on_device == 0).  Packs them into the library's per-parity layout in the
- * precisions selected by storage_flags.  Invalidates the clover term. */
+ * U_on_device == 0; read in place where they lie 16-byte aligned in the memory of the
+ * lattice's GPU, else through a copy).  Packs them into the library's per-parity layout in the
+ * precisions selected by storage_flags, on the lattice's stream.  Invalidates the clover term. */
 int ddq_set_gauge(ddq_lattice* lat, const void* U, int U_on_device, unsigned storage_flags);
 
 /* Builds the clover blocks A(x) on the GPU in FP64 (Sect. 2.3 operator), keeps
@@ -506,7 +507,7 @@ int ddq_batch_destroy(ddq_batch* batch);
  *   are differentiated.  accumulate != 0 adds to G / F instead of overwriting.
  *   chi_e, phi_e: FP64 parity vectors.  Needs the canonical links set by
  *   ddq_set_gauge and the clover of ddq_set_clover.  Work space (two parity
- *   vectors and V x 54 complex128 insertions): DDQ_RESERVE_FORCE of ddq_reserve. */
+ *   vectors and 480 bytes of insertions a site): DDQ_RESERVE_FORCE of ddq_reserve. */
 int ddq_backward_apply(ddq_lattice* lat, int prec, int nrhs, const void* grad_y_e, void* grad_x_e);
 int ddq_backward_link_force(ddq_lattice* lat, const void* chi_e, const void* phi_e, void* G, void* F,
                             int accumulate);

@@ -1308,6 +1308,7 @@ int ddq_oe_prepare(ddq_lattice* L, int nrhs, const void* b, void* bt_e) {
   CHK(check_ready(L, DDQ_F64));
   if (nrhs < 1 || !b || !bt_e) return fail(DDQ_ERR_ARG, "bad prepare arguments");
   if (b == bt_e) return fail(DDQ_ERR_ARG, "b and bt_e must not overlap");
+  // needs no scratch; a count beyond the reservation is refused, as it is by reconstruct
   CHK(L->scratch64.ensure((size_t)nrhs * L->nvec() * 16));
   return prepare_impl(L, nrhs, (const d2_t*)b, (d2_t*)bt_e);
 }
@@ -1317,7 +1318,7 @@ int ddq_oe_reconstruct(ddq_lattice* L, int nrhs, const void* x_e, const void* b,
   if (nrhs < 1 || !x_e || !b || !x) return fail(DDQ_ERR_ARG, "bad reconstruct arguments");
   if (x == b || x == x_e) return fail(DDQ_ERR_ARG, "x must not overlap b or x_e");
   const size_t nb = (size_t)nrhs * L->nvec();
-  CHK(L->scratch64.ensure(2 * nb * 16));
+  CHK(L->scratch64.ensure(2 * nb * 16));  // needs none: the reservation bounds the count
   return reconstruct_impl(L, nrhs, (const d2_t*)x_e, (const d2_t*)b, (d2_t*)x);
 }
 

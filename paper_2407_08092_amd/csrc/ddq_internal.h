@@ -144,7 +144,7 @@ template <typename R>
 hipError_t launch_hop_stream(const HopArgs<R>& a, int mode, hipStream_t s);
 
 // the same launches (no tile; M_PREP and M_RECON only here) on four threads per site, bit for bit the results of
-// launch_hop and launch_hop16: for launches of few sites (hop_split.hip)
+// launch_hop and launch_hop16: for launches of few sites or of several right-hand sides (hop_split.hip)
 bool hop_split_takes(const Geo& g, int bytes_per_complex, int nrhs, bool sweep);
 template <typename R>
 hipError_t launch_hop_split(const HopArgs<R>& a, int mode, bool dagger, int nrhs, hipStream_t s);

@@ -259,11 +259,11 @@ __device__ __forceinline__ bool hpd_inverse6(cpx<double> (&A)[6][6], const cpx<d
 //
 // A workgroup is 64 sites of one parity x 6 wavefronts, one per plane; the six F meet in LDS,
 // from which two wavefronts (one per block) form, and on odd sites invert, the 6x6 blocks.
-// Bound by the latency of the links (one product at a time, three wavefronts a SIMD): 16^3 x 32
-// 225 us (one thread a site on canonical links, 464 B of scratch, and 2 x 17 us for the FP32 copy)
-// -> 119.  Few sites in flight matter more than registers: four wavefronts with three planes each
-// of both parities read 506 MB past L2 against 165 here, and took the same 93 us with twice the
-// matrices in flight.
+// Bound by the latency of the links (one product at a time, three wavefronts a SIMD, 52 B of
+// scratch): 16^3 x 32 225 us (one thread a site on canonical links, 464 B of scratch, and 2 x 17 us
+// for the FP32 copy) -> 119.  With leaves of 10 products, four wavefronts with three planes each of
+// both parities, twice the matrices in flight, read 506 MB past L2 against 165 and took 93 us
+// against 96.
 constexpr int CLOVER_PLANES = 6;
 __global__ void __launch_bounds__(64 * CLOVER_PLANES) __attribute__((amdgpu_waves_per_eu(3)))
 k_clover_build(Geo g, PackedLinks L, double c_sw, double m0, ClovOut out, int* notpd) {

@@ -202,7 +202,7 @@ __device__ __forceinline__ C3 hop_terms(const ParityPair& av, const ParityPair& 
 // from which the links leave in canonical order (144 contiguous bytes a link).
 // Bound by the FP64 units (14 3x3 products a plane: about 80 us of issue at 16^3 x 32) and by L2
 // misses, which follow the number of sites in flight: 16^3 x 32 361 us (canonical links, one
-// thread a link) -> 164 (234 registers, two wavefronts a SIMD, 718 MB past L2).  Measured
+// thread a link) -> 164 to 171 (234 registers, two wavefronts a SIMD, 718 MB past L2).  Measured
 // beside it: links through both packed copies 186 us (1.09 GB); one plaquette at a time in 164
 // registers, three wavefronts a SIMD 196 (1.26 GB); twelve wavefronts a group of 64 sites, one
 // plane each 189 (555 MB, but 15 % more instructions and a barrier); both links of a plane in one

@@ -1,5 +1,5 @@
-// hop_split.hip -- the stencil of hop.hip / hop_h16.hip for launches of few sites: four
-// threads per output site, one per direction.
+// hop_split.hip -- the stencil of hop.hip / hop_h16.hip for launches of few sites or of several
+// right-hand sides: four threads per output site, one per direction.
 //
 // The one-thread-per-site kernels walk a site's eight hops one after the other with one
 // hop's loads in flight, about eight memory latencies per wavefront.  A large lattice hides

@@ -85,10 +85,12 @@ def random_vectors(lat, n, dtype, seed):
 # One right-hand side, on both sides of every line of the size rules and in every cache policy, in
 # one launch and in ranges of t-slices, against launches of two, which take four threads a site
 # (16 bits: one, two vectors a thread).  Sites of a parity / what one takes:
+#   5,760: four threads a site, nine groups of 64 sites a slice in a row (two vectors: slab order);
 #   44,000: one thread a site but for FP32 sweeps; 69,696: FP32 four threads again, 16 bits one;
 #   216,000: FP32 sweeps stream links and results; 405,000: FP32 one thread, vectors kept;
 #   629,440: FP64 streams; 1,207,184: FP32 streams
 @pytest.mark.parametrize("dims, dtypes", [
+    ((18, 8, 8, 10), DTYPES),
     ((20, 22, 10, 20), (torch.complex128, torch.complex64)),
     ((22, 22, 18, 16), DTYPES),
     ((30, 30, 30, 16), (torch.complex128, torch.complex64)),
