@@ -288,7 +288,7 @@ hipError_t launch_any(ddq_lattice* L, const HopArgs<R>& a, int mode, bool dag, i
       return launch_hop_rb(b, mode, nrhs, L->stream);
     }
   }
-  if (mode == M_PREP || mode == M_RECON || (!t && hop_split_takes(L->geo, sizeof(pair<R>), nrhs, a.sweep)))
+  if (mode == M_PREP || mode == M_RECON || (!t && hop_split_takes(L->geo, sizeof(pair<R>), nrhs, a.reuse)))
     return launch_hop_split<R>(a, mode, dag, nrhs, L->stream);
   // one right-hand side per thread: the workgroup order of an nb = 0 tile set for
   // nrhs, else slab order
@@ -371,12 +371,12 @@ hipError_t run_hop16(ddq_lattice* L, int prec, int nrhs, int mode, const void* i
   a.out = (u4_t*)out;
   a.omega = omega;
   a.nrhs = nrhs;
-  a.sweep = sweep;
+  a.reuse = sweep ? REUSE_SWEEP : REUSE_NONE;
   // workgroup order: that of the lattice's FP32 tile for this count, else slab order
   const MrTile* t = nrhs > 1 ? L->tile_for(nrhs) : nullptr;
   a.chunk = t ? t->xmap : XMAP_SLAB;
   auto launch = [&]() {
-    return !t && hop_split_takes(L->geo, 4, nrhs, sweep) ? launch_hop16_split(h16_kind(prec), a, mode, L->stream)
+    return !t && hop_split_takes(L->geo, 4, nrhs, a.reuse) ? launch_hop16_split(h16_kind(prec), a, mode, L->stream)
                                                   : launch_hop16(h16_kind(prec), a, mode, L->stream);
   };
   if (!L->prof_on || g_no_alloc_call) return launch();
@@ -449,9 +449,10 @@ HopArgs<R> hop_args(const ddq_lattice* L, int prec, int p_out) {
 
 // u_o = A_oo^-1 H_oe x_e  (kernel A)
 template <typename R>
-hipError_t kernel_A(ddq_lattice* L, int prec, int nrhs, const pair<R>* x, pair<R>* u, bool dag, bool sweep = false) {
+hipError_t kernel_A(ddq_lattice* L, int prec, int nrhs, const pair<R>* x, pair<R>* u, bool dag,
+                    FieldReuse reuse = REUSE_NONE) {
   HopArgs<R> a = hop_args<R>(L, prec, 1);
-  a.sweep = sweep;
+  a.reuse = reuse;
   a.in = x;
   a.out = u;
   return run_hop<R>(L, a, M_HOP_CLINV, dag, nrhs);
@@ -460,14 +461,14 @@ hipError_t kernel_A(ddq_lattice* L, int prec, int nrhs, const pair<R>* x, pair<R
 // even-side kernel B in one of its modes
 template <typename R>
 hipError_t kernel_B(ddq_lattice* L, int prec, int nrhs, int mode, const pair<R>* u, const pair<R>* x,
-                    const pair<R>* b, pair<R>* out, R omega, bool dag) {
+                    const pair<R>* b, pair<R>* out, R omega, bool dag, FieldReuse reuse = REUSE_NONE) {
   HopArgs<R> a = hop_args<R>(L, prec, 0);
   a.in = u;
   a.x = x;
   a.b = b;
   a.out = out;
   a.omega = omega;
-  a.sweep = mode == M_RICH;
+  a.reuse = mode == M_RICH ? REUSE_SWEEP : reuse;
   return run_hop<R>(L, a, mode, dag, nrhs);
 }
 
@@ -500,7 +501,7 @@ int sweep_chunked(ddq_lattice* L, int prec, const pair<R>* x, const pair<R>* b, 
     HopArgs<R> a = hop_args<R>(L, prec, 1);
     a.in = x;
     a.out = u;
-    a.sweep = mode == M_RICH;
+    a.reuse = mode == M_RICH ? REUSE_SWEEP : REUSE_NONE;
     a.t_lo = lo(c);
     a.t_cnt = lo(c + 1) - lo(c);
     return run_hop<R>(L, a, M_HOP_CLINV, dag, 1);
@@ -512,7 +513,7 @@ int sweep_chunked(ddq_lattice* L, int prec, const pair<R>* x, const pair<R>* b, 
     a.b = b;
     a.out = out;
     a.omega = omega;
-    a.sweep = mode == M_RICH;
+    a.reuse = mode == M_RICH ? REUSE_SWEEP : REUSE_NONE;
     a.t_lo = lo(c);
     a.t_cnt = lo(c + 1) - lo(c);
     return run_hop<R>(L, a, mode, dag, 1);
@@ -529,12 +530,13 @@ int sweep_chunked(ddq_lattice* L, int prec, const pair<R>* x, const pair<R>* b, 
 
 // u: work space for u_o (nrhs parity vectors of prec); null selects the lattice's own
 template <typename R>
-int schur(ddq_lattice* L, int prec, int nrhs, const pair<R>* x, pair<R>* y, bool dag, pair<R>* u = nullptr) {
+int schur(ddq_lattice* L, int prec, int nrhs, const pair<R>* x, pair<R>* y, bool dag, pair<R>* u = nullptr,
+          FieldReuse reuse = REUSE_NONE) {
   if (!u) u = (pair<R>*)L->tmp[prec].p;
   const int nc = nrhs == 1 ? chunks_for(L, prec) : 1;
   if (nc > 1) return sweep_chunked<R>(L, prec, x, nullptr, u, y, R(0), nc, M_APPLY, dag);
-  HIPCHK(kernel_A<R>(L, prec, nrhs, x, u, dag));
-  HIPCHK(kernel_B<R>(L, prec, nrhs, M_APPLY, u, x, nullptr, y, R(0), dag));
+  HIPCHK(kernel_A<R>(L, prec, nrhs, x, u, dag, reuse));
+  HIPCHK(kernel_B<R>(L, prec, nrhs, M_APPLY, u, x, nullptr, y, R(0), dag, reuse));
   return DDQ_OK;
 }
 
@@ -555,7 +557,7 @@ int sweeps(ddq_lattice* L, int prec, int nrhs, pair<R>* x, const pair<R>* b, int
       CHK(sweep_chunked<R>(L, prec, x, b, u, x, omega, nc, M_RICH, false));
       continue;
     }
-    HIPCHK(kernel_A<R>(L, prec, nrhs, x, u, false, true));
+    HIPCHK(kernel_A<R>(L, prec, nrhs, x, u, false, REUSE_SWEEP));
     HIPCHK(kernel_B<R>(L, prec, nrhs, M_RICH, u, x, b, x, omega, false));
   }
   return DDQ_OK;
@@ -1291,7 +1293,7 @@ int ddq_estimate_lambda_max(ddq_lattice* L, int iters, const void* v0, double* o
   CHK(norm2_dev(L, (const d2_t*)v0, n, nrm));
   HIPCHK(launch_scale_dev(v, (const d2_t*)v0, nrm, n, L->stream));
   for (int k = 0; k < iters; ++k) {
-    CHK(schur<double>(L, DDQ_F64, 1, v, w, false));
+    CHK(schur<double>(L, DDQ_F64, 1, v, w, false, nullptr, REUSE_SOLVE));
     CHK(norm2_dev(L, w, n, nrm + 1 + k));
     HIPCHK(launch_scale_dev(v, w, nrm + 1 + k, n, L->stream));
   }
@@ -1822,7 +1824,7 @@ int oe_solve_one(ddq_lattice* L, void* x, const void* b, const ddq_gmres_params*
         }
         HIPCHK(launch_parity_to_f64(zk, x32, 1, (int)L->Vh, L->stream));
       }
-      CHK(schur<float>(L, DDQ_F32, 1, x32, w32, false));
+      CHK(schur<float>(L, DDQ_F32, 1, x32, w32, false, nullptr, REUSE_SOLVE));
       ++applies_lo;
       HIPCHK(launch_parity_to_f64(ww, w32, 1, (int)L->Vh, L->stream));
     } else {
@@ -1830,7 +1832,7 @@ int oe_solve_one(ddq_lattice* L, void* x, const void* b, const ddq_gmres_params*
         CHK(rich_prec_impl(L, 1, vk, zk, nu, P->omega, DDQ_F64, nullptr, nullptr));
         applies64 += nu - 1;
       }
-      CHK(schur<double>(L, DDQ_F64, 1, zk, ww, false));
+      CHK(schur<double>(L, DDQ_F64, 1, zk, ww, false, nullptr, REUSE_SOLVE));
       ++applies64;
     }
     return DDQ_OK;
@@ -2254,7 +2256,7 @@ int batch_step(ddq_batch* B, int k, int nu) {
       HIPCHK(launch_parity_to_f32(S.x32, vk, S.nrhs, vh, B->stream));
     }
     HIPCHK(launch_parity_to_f64(zk, S.x32, S.nrhs, vh, B->stream));
-    CHK(schur<float>(L, DDQ_F32, S.nrhs, (const f2_t*)S.x32, (f2_t*)S.w32v, false));
+    CHK(schur<float>(L, DDQ_F32, S.nrhs, (const f2_t*)S.x32, (f2_t*)S.w32v, false, nullptr, REUSE_SOLVE));
     HIPCHK(launch_parity_to_f64(S.w, S.w32v, S.nrhs, vh, B->stream));
     // classical Gram-Schmidt, one or two passes (h1 = V^H w, w -= V h1, and again
     // with h2), then |w|^2

@@ -112,9 +112,13 @@ struct HopArgs {
   int nrhs;                  // right-hand sides of the launch
   long long rhs_stride;      // complex elements between right-hand sides
   MrTile tile;               // FP32 multi-right-hand-side tile (nb = 0: one right-hand side per thread)
-  bool sweep;                // part of a Richardson sweep: the next launches read the same fields (cache_policy)
+  int reuse;                 // FieldReuse of the launch
   int t_lo, t_cnt;           // one right-hand side: only output sites of slices [t_lo, t_lo + t_cnt) (t_cnt 0: all)
 };
+
+// Whether the launches that follow read the same fields: not that the library knows (an apply, eq. 2),
+// the applies of a solve, a Richardson sweep.
+enum FieldReuse { REUSE_NONE = 0, REUSE_SOLVE = 1, REUSE_SWEEP = 2 };
 
 // Cache policy of a sweep's launches on vh sites a parity with one right-hand side (a single
 // apply's results are not read by the launches that follow and stream: kept, 24^3 x 48 FP64 272
@@ -125,8 +129,8 @@ struct HopArgs {
 // 12-real 32^3 x 64 (302 MB) 381 -> 339; FP16 24^3 x 48 (127 MB of vectors and clover) 65 -> 60,
 // 24^3 x 96 (308 MB) 121 -> 110, 48^3 x 96 (764 MB of vectors: streams) 909, kept 975.
 constexpr long long CACHE_FIELDS = 320LL << 20;
-inline int cache_policy(bool sweep, int vh, int vec, int clov) {
-  if (!sweep) return CP_STREAM;
+inline int cache_policy(int reuse, int vh, int vec, int clov) {
+  if (reuse != REUSE_SWEEP) return CP_STREAM;
   const long long v = 3LL * vh * vec, c = 2LL * vh * clov;
   return v + c <= CACHE_FIELDS ? CP_VECTORS_CLOVER : v <= CACHE_FIELDS ? CP_VECTORS : CP_STREAM;
 }
@@ -145,7 +149,7 @@ hipError_t launch_hop_stream(const HopArgs<R>& a, int mode, hipStream_t s);
 
 // the same launches (no tile; M_PREP and M_RECON only here) on four threads per site, bit for bit the results of
 // launch_hop and launch_hop16: for launches of few sites or of several right-hand sides (hop_split.hip)
-bool hop_split_takes(const Geo& g, int bytes_per_complex, int nrhs, bool sweep);
+bool hop_split_takes(const Geo& g, int bytes_per_complex, int nrhs, int reuse);
 template <typename R>
 hipError_t launch_hop_split(const HopArgs<R>& a, int mode, bool dagger, int nrhs, hipStream_t s);
 
@@ -207,7 +211,7 @@ struct Hop16Args {
   float omega;
   int nrhs;
   int nb;     // right-hand sides per thread, 1..3 (0: the largest of 3, 2, 1 dividing nrhs)
-  bool sweep;  // part of a Richardson sweep (cache_policy)
+  int reuse;  // FieldReuse
   int chunk;  // XCD order of the workgroups (tile_site): 0 dispatcher order, c > 0 chunks, XMAP_SLAB
 };
 hipError_t launch_hop16(int kind, const Hop16Args& a, int mode, hipStream_t s);

@@ -279,7 +279,7 @@ static hipError_t launch_mode(const HopArgs<R>& a, bool dagger, int nrhs, hipStr
   // a sweep's launches; in FP32 those that reach this kernel are past the sites whose clover blocks fit
   if constexpr (MODE == M_HOP_CLINV || MODE == M_RICH) {
     if (nrhs == 1 && !dagger) {
-      const int cp = cache_policy(a.sweep, a.g.Vh, SPINOR_ROWS * (int)sizeof(pair<R>), CLOVER_ROWS * (int)sizeof(pair<R>));
+      const int cp = cache_policy(a.reuse, a.g.Vh, SPINOR_ROWS * (int)sizeof(pair<R>), CLOVER_ROWS * (int)sizeof(pair<R>));
       if constexpr (!F32) {
         if (cp == CP_VECTORS_CLOVER) {
           DDQ_HOP_LAUNCH(false, false, false, CP_VECTORS_CLOVER);

@@ -207,7 +207,7 @@ static hipError_t launch16_nb(const Hop16Args& a, int mode, hipStream_t s) {
   return a.clov32 ? launch16_c<S, NB, true, CP>(a, mode, grid, block, s) : launch16_c<S, NB, false, CP>(a, mode, grid, block, s)
   if constexpr (NB == 1) {
     if (a.nrhs == 1 && mode != M_APPLY) {
-      const int cp = cache_policy(a.sweep, a.g.Vh, SP16_E * 16, a.clov32 ? CLOVER_ROWS * 8 : CL16_E * 16);
+      const int cp = cache_policy(a.reuse, a.g.Vh, SP16_E * 16, a.clov32 ? CLOVER_ROWS * 8 : CL16_E * 16);
       if (cp == CP_VECTORS_CLOVER) DDQ_H16_LAUNCH(CP_VECTORS_CLOVER);
       if (cp == CP_VECTORS) DDQ_H16_LAUNCH(CP_VECTORS);
     }

@@ -75,6 +75,7 @@ struct SplitR {
     }
   }
   static __device__ __forceinline__ cpx<R> stored(cpx<R> c) { return c; }
+  static __device__ __forceinline__ cpx<R> formed_here(cpx<R> c) { return c; }
   static __device__ __forceinline__ void put(const Field& v, int r, uint32_t off, cpx<R> c) {
     if constexpr (CPE<R> == 1) {
       __builtin_amdgcn_raw_buffer_store_b128(pack<R>(&c), v.rsrc, (int)off, (int)(r * v.row_bytes), ST_AUX);
@@ -123,8 +124,8 @@ struct Split16 {
         __builtin_amdgcn_raw_buffer_load_b32(v.rsrc, (int)(off + 4u * (r & 3)), (int)((r >> 2) * v.row_bytes), 0);
     return {h2f<S>((u16_t)(q & 0xffffu)), h2f<S>((u16_t)(q >> 16))};
   }
-  static __device__ __forceinline__ unsigned stored(cpx<R> c) {
-    unsigned q = (unsigned)f2h<S>(c.r) | ((unsigned)f2h<S>(c.i) << 16);
+  static __device__ __forceinline__ unsigned stored(cpx<R> c) { return (unsigned)f2h<S>(c.r) | ((unsigned)f2h<S>(c.i) << 16); }
+  static __device__ __forceinline__ unsigned formed_here(unsigned q) {
     asm("" : "+v"(q));
     return q;
   }
@@ -199,7 +200,7 @@ struct SplitArgs {
   double omega;
   int nrhs;
   int dagger;
-  int sweep;        // part of a Richardson sweep (split_policy)
+  int reuse;        // FieldReuse
   int slab;         // slab order; else the groups of 64 sites in a row
   int t_lo, t_cnt;  // output sites of slices [t_lo, t_lo + t_cnt)
   // M_PREP, M_RECON: b is a full FP64 vector
@@ -318,7 +319,7 @@ hop_split_kernel(SplitArgs a) {
       clover_rows<half.value, R>(sl, v6, o);
       if constexpr (MODE == M_HOP_CLINV)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) y[c] = P::stored(o[c]);
+        for (int c = 0; c < 3; ++c) y[c] = P::formed_here(P::stored(o[c]));
     };
     if (w & 1)
       rows3(std::integral_constant<int, 1>{});
@@ -421,7 +422,8 @@ static hipError_t split_launch(SplitArgs a, int mode, hipStream_t s) {
 //     139 -> 125 / 142 -> 133 / 150 -> 148 / 139 -> 135; 28^3 x 32 143 -> 143 / 149 -> 147 / 158 -> 157 /
 //     144 -> 148); between them 1 GB written just before costs up to 8 % (24^2 x 20 x 32 78 -> 69 / 79 ->
 //     70 / 84 -> 91 / 78 -> 80).  Sweeps to 400,000 sites: two on 16^3 x 32 63 -> 57, on 24^3 x 48 287 -> 250,
-//     on 387,072 sites 308 -> 303;
+//     on 387,072 sites 308 -> 303.  A solve's applies, whose fields the steps before left: 16^3 x 32
+//     with nothing streamed 29 (the mixed solve there 3.99 ms -> 3.89);
 //   several: the wavefronts of one 64-site group follow each other and take links and clover
 //     from L2, at every size measured.  FP32 (no tile set): 2 on 16^3 x 32 51 -> 36 / 52 -> 36 / 55 -> 60 /
 //     51 -> 45, 4 on 32^4 571 -> 575 (the closest: the one-thread kernel takes four together) and on
@@ -433,14 +435,15 @@ static hipError_t split_launch(SplitArgs a, int mode, hipStream_t s) {
 //     two and three do not divide, where it shares nothing and has the more wavefronts: 5 on 4,608
 //     15 -> 14 and on 10,368 16 -> 18, 7 on 4,096 17 -> 13 and on 4,608 15 -> 17.
 // And four threads a site reach a launch's limit of threads at a quarter of the sites.
-bool hop_split_takes(const Geo& g, int bytes_per_complex, int nrhs, bool sweep) {
+bool hop_split_takes(const Geo& g, int bytes_per_complex, int nrhs, int reuse) {
   const long long n = (long long)g.Vh * nrhs;
   if (split_grid(g, g.L[3], nrhs) > SPLIT_MAX_GRID) return false;
   if (bytes_per_complex == 4)
     return n <= (nrhs == 1 || nrhs > 9 ? 65536 : nrhs % 2 != 0 && nrhs % 3 != 0 ? 24576 : 98304);
   if (nrhs > 1) return true;
   if (bytes_per_complex == 16) return n <= 40960;
-  return sweep ? n <= 400000 : n <= 40960 || (n > 65536 && n <= 340000);
+  if (reuse == REUSE_NONE) return n <= 40960 || (n > 65536 && n <= 340000);
+  return n <= (reuse == REUSE_SOLVE ? 340000 : 400000);
 }
 
 // What a launch streams past the Infinity Cache.  A line that is allocated there pushes another one
@@ -449,15 +452,14 @@ bool hop_split_takes(const Geo& g, int bytes_per_complex, int nrhs, bool sweep) 
 //   above, nothing streamed -> links: 16^4 18 -> 19 / 19 -> 20 / 29 -> 23 / 21 -> 20, 24^3 x 32 95 -> 79 /
 //   97 -> 79 / 127 -> 105 / 98 -> 96; FP16 16^3 x 32 19 -> 20 / 20 -> 21 / 26 -> 23 / 21 -> 21.  The results
 //   too: 24^3 x 32 84 / 84 / 116 / 99; clover blocks, which two wavefronts read, too: 16^3 x 32 31 -> 35.
-// * One right-hand side in a sweep, whose next launches read the same fields: nothing where the
-//   links and clover blocks of both parities fit the cache's 256 MB, else links and results (24^3 x 48
-//   six FP32 sweeps 739, links only 778, nothing 852).
+// * One right-hand side in a sweep or a solve, whose next launches read the same fields: nothing where
+//   the links and clover blocks of both parities fit the cache's 256 MB, else a sweep's links and
+//   results (24^3 x 48 six FP32 sweeps 739, links only 778, nothing 852) and an apply's links.
 // * Several: nothing; the next wavefronts read the links again (streamed with the results: 2 on 32^4
 //   FP32 329 -> 342, 4 575 -> 617, 8 on 32^3 x 64 FP64 4154 -> 4474).
 static int split_policy(const SplitArgs& a, long long field_bytes) {
-  if (a.nrhs > 1) return ST_NONE;
-  if (!a.sweep) return ST_LINKS;
-  return field_bytes <= (256LL << 20) ? ST_NONE : ST_LINKS_RESULT;
+  if (a.nrhs > 1 || (a.reuse != REUSE_NONE && field_bytes <= (256LL << 20))) return ST_NONE;
+  return a.reuse == REUSE_SWEEP ? ST_LINKS_RESULT : ST_LINKS;
 }
 
 template <typename R, bool L12>
@@ -485,7 +487,7 @@ hipError_t launch_hop_split(const HopArgs<R>& h, int mode, bool dagger, int nrhs
   a.omega = (double)h.omega;
   a.nrhs = nrhs;
   a.dagger = dagger ? 1 : 0;
-  a.sweep = h.sweep;
+  a.reuse = h.reuse;
   a.t_lo = h.t_lo;
   a.t_cnt = h.t_cnt;
   a.full = h.full;
@@ -520,7 +522,7 @@ hipError_t launch_hop16_split(int kind, const Hop16Args& h, int mode, hipStream_
   a.omega = (double)h.omega;
   a.nrhs = h.nrhs;
   if (h.nrhs < 1) return hipErrorInvalidValue;
-  a.sweep = h.sweep;
+  a.reuse = h.reuse;
   return kind == H16_BF16 ? split_launch_16<__bf16>(a, h.clov32 != nullptr, mode, s) : split_launch_16<_Float16>(a, h.clov32 != nullptr, mode, s);
 }
 
