@@ -1120,6 +1120,8 @@ int ddq_set_multi_rhs_tile(ddq_lattice* L, int nrhs, const ddq_mr_tile* tile) {
   return DDQ_OK;
 }
 
+constexpr double TUNE_NOISE_MS = 0.002;  // of a sweep timed with two repetitions
+
 int ddq_tune_multi_rhs(ddq_lattice* L, int nrhs, int reps, ddq_mr_tile* results, int max_results, int* n_results,
                        ddq_mr_tile* chosen) {
   CHK(check_ready(L, DDQ_F32));
@@ -1168,7 +1170,10 @@ int ddq_tune_multi_rhs(ddq_lattice* L, int nrhs, int reps, ddq_mr_tile* results,
     if (rc == DDQ_OK && (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
       rc = fail(DDQ_ERR_HIP, "event timing");
     cand[k].ms = ms / reps;
-    if (rc == DDQ_OK && cand[k].ms < cand[best].ms) best = k;
+    // a tile with passes or an LDS cap has to win by more than two runs of one tile differ: on a
+    // lattice of some thousand sites the launches take all the time and the first of equals is as good
+    const bool plain = cand[k].passes == 1 && cand[k].lds_kb == 0;
+    if (rc == DDQ_OK && cand[k].ms < cand[best].ms - (plain ? 0.0 : TUNE_NOISE_MS)) best = k;
   }
   L->prof_on = prof;
   (void)hipEventDestroy(e0);
