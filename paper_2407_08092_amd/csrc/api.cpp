@@ -862,6 +862,7 @@ int ddq_set_clover(ddq_lattice* L, double c_sw, double m0) {
   L->have_clover = false;
   L->sap_prec = -1;
   L->sap_res_ok = false;
+  const bool first = !L->clov[DDQ_F64][0];
   const size_t n = (size_t)36 * field_vh((int)L->Vh);  // (re, im) slots per parity
   for (int q = 0; q < 2; ++q)
     if (!L->clov[DDQ_F64][q]) {
@@ -898,6 +899,11 @@ int ddq_set_clover(ddq_lattice* L, double c_sw, double m0) {
                                   L->stream));
     }
   }
+  // On a new lattice the wait above ends a long batch (whatever made the links), whose commands the
+  // runtime then retires one by one; the next call that frees memory, a reservation that grows,
+  // would wait for that.  A short batch behind it is retired here: first apply to three right-hand
+  // sides on a new 12 x 10 x 6 x 14 lattice 160 -> 104 us, this call + 12 us.
+  if (first) HIPCHK(hipMemsetAsync(L->small.p, 0, sizeof(double), L->stream));
   HIPCHK(hipStreamSynchronize(L->stream));
   L->c_sw = c_sw;
   L->m0 = m0;

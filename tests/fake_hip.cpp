@@ -10,7 +10,7 @@ struct Dim3 {
   uint32_t x, y, z;
 };
 struct Event {
-  int kind;  // 0: copy, 1: kernel
+  int kind;  // 0: copy, 1: kernel, 2: memset, 3: wait for a stream
   const char* name;
   const void* ptr;  // copy: the source; kernel: its second argument
   uint64_t grid, block;
@@ -61,8 +61,14 @@ int hipGetDevice(int* d) {
 }
 int hipGetSymbolAddress(void** p, const void*) { return hipMalloc(p, 4096); }
 int hipGetLastError() { return 0; }
-int hipStreamSynchronize(void*) { return 0; }
-int hipMemsetAsync(void*, int, size_t, void*) { return 0; }
+int hipStreamSynchronize(void*) {
+  record({3, "wait", nullptr, 0, 0});
+  return 0;
+}
+int hipMemsetAsync(void* p, int, size_t, void*) {
+  record({2, "memset", p, 0, 0});
+  return 0;
+}
 int hipMemcpyAsync(void*, const void* src, size_t, int, void*) {
   record({0, "copy", src, 0, 0});
   return 0;

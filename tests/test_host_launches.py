@@ -50,6 +50,21 @@ def applies(fake, L, dims, nrhs, prec):
     return [e for e in events(fake) if e["kind"] == 1]
 
 
+def clover_twice(fake, L):
+    """What ddq_set_clover enqueues and waits for after the clover build, on a new lattice and again."""
+    h = lattice(L, (4, 4, 4, 4))
+    fake.fake_pointer(0, DEVICE, 0)
+    out = []
+    for _ in range(2):
+        assert L.ddq_set_gauge(h, C.c_void_p(U), 1, 1 | 2) == 0, L.ddq_last_error()
+        events(fake)
+        assert L.ddq_set_clover(h, 1.0, 0.1) == 0, L.ddq_last_error()
+        e = events(fake)
+        build = max(k for k, v in enumerate(e) if "k_clover_build" in v["name"])
+        out.append([v["name"] for v in e[build + 1:]])
+    return out
+
+
 def main(fake_path, call, args):
     fake = C.CDLL(fake_path, mode=C.RTLD_GLOBAL)
     fake.fake_events.restype = C.POINTER(Event)
@@ -98,6 +113,10 @@ def test_a_launch_stays_below_the_limit_of_threads(run, dims, nrhs, split):
     for e in ev:
         assert e["grid"] * e["block"] < 2**32
         assert ("hop_split_kernel" in e["name"]) == split
+
+
+def test_a_new_lattices_clover_leaves_no_batch_to_retire(run):
+    assert run("clover_twice") == [["wait", "memset", "wait"], ["wait", "wait"]]
 
 
 if __name__ == "__main__":
